@@ -142,6 +142,16 @@ inline int ceil_log2(int64_t x) {
     return r;
 }
 
+// Workgroup barrier that orders LDS accesses only: global loads issued before
+// it may still be in flight after it (__syncthreads waits for them too).  The
+// fences name the LDS address space; global memory written before it is not
+// made visible to the other waves.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ------------------------------------------------------------------ histogram
 
 constexpr int HIST_LDS_BINS = 4096;  // bins a workgroup counts in LDS before one global add per bin

@@ -53,6 +53,28 @@ def test_graph_weights_match_oracle(iso, orc, name, phi):
     np.testing.assert_array_equal(p0.cpu().numpy(), ref_p0)
 
 
+@pytest.mark.parametrize("n,d", [(2, 1), (63, 5), (65, 16), (2049, 3), (4097, 2), (5003, 17)])
+@pytest.mark.parametrize("which", ["both", "omega", "p0"])
+def test_graph_weights_blocks(iso, orc, n, d, which):
+    """Sizes at the edges of the tiles and of the column blocks (one block up to
+    2,048 points, then two to three ragged ones), each output alone and both,
+    with a strided input; p0 bit for bit, omega0 to the exponentials' ulp."""
+    H.log("graph weights blocks n=%d d=%d %s" % (n, d, which))
+    X = datagen.uniform(n, d, seed=n)
+    parent = np.zeros(n, np.int32)
+    parent[0] = -1
+    length = np.ones(n)
+    phi = "gauss_sq" if n % 2 == 0 else "exp"
+    _, ref_om, ref_p0 = orc.tree_weights(parent, length, 0.3, omega="full", phi=phi, alpha_pot=0.05, X=X)
+    Xg = torch.zeros(n, d + 3, device="cuda")
+    Xg[:, :d] = torch.from_numpy(X).cuda()
+    om, p0 = iso.graph_weights(Xg[:, :d], 0.3, phi=phi, alpha=0.05, omega=which != "p0", potential=which != "omega")
+    if which != "p0":
+        np.testing.assert_allclose(om.cpu().numpy(), ref_om, rtol=1e-13, atol=0)
+    if which != "omega":
+        np.testing.assert_array_equal(p0.cpu().numpy(), ref_p0)
+
+
 def test_sigma_median(iso, orc):
     X, p, l, sigma = _tree(orc, "c1-n2000-d16")
     assert iso.sigma_median(torch.from_numpy(p).cuda(), torch.from_numpy(l).cuda()) == sigma
