@@ -259,66 +259,157 @@ void radix_sort_pairs_u32(uint32_t *keys, uint32_t *vals, uint32_t *tmp_keys, ui
 
 // ------------------------------------------------------------------ radix select (FP64 >= 0)
 
+// Digits of 11 bits from the top (the last one 9 bits): six rounds.  Up to
+// SEL_SMALL values one workgroup runs every round in one launch; more take one
+// launch per round, in which the workgroup that finishes last (a counter)
+// picks the digit, so that no second launch is needed for it.
+constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS;
+constexpr int64_t SEL_SMALL = 16384;
+constexpr int SEL_ROUNDS = 6;
+
 struct SelState {
     uint64_t prefix;
     uint64_t mask;
     int64_t rank;
-    int32_t hist[256];
+    int32_t finished, pad;
+    int32_t hist[SEL_BINS];
 };
 
+__device__ inline void sel_digit(int round, int &shift, int &bits) {
+    shift = round + 1 < SEL_ROUNDS ? 64 - SEL_BITS * (round + 1) : 0;
+    bits = round + 1 < SEL_ROUNDS ? SEL_BITS : 64 - SEL_BITS * (SEL_ROUNDS - 1);
+}
+
+// The digit that holds rank r of the histogram h, by a workgroup of 256; the
+// rank within it in *r_out.
+__device__ inline int sel_pick(const int32_t *h, int64_t r, int64_t *r_out) {
+    __shared__ int32_t part[256];
+    __shared__ int s_digit;
+    __shared__ int64_t s_rank;
+    constexpr int PER = SEL_BINS / 256;
+    const int tid = threadIdx.x;
+    int32_t x[PER], sum = 0;
+    for (int u = 0; u < PER; ++u) {
+        x[u] = h[tid * PER + u];
+        sum += x[u];
+    }
+    part[tid] = sum;
+    if (tid == 0) {
+        s_digit = SEL_BINS - 1;
+        s_rank = r;
+    }
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {
+        const int32_t o = tid >= off ? part[tid - off] : 0;
+        __syncthreads();
+        part[tid] += o;
+        __syncthreads();
+    }
+    int64_t before = (int64_t)part[tid] - sum;
+    if (r >= before && r < before + sum) {
+        int u = 0;
+        while (r >= before + x[u]) before += x[u++];
+        s_digit = tid * PER + u;
+        s_rank = r - before;
+    }
+    __syncthreads();
+    *r_out = s_rank;
+    return s_digit;
+}
+
 __global__ __launch_bounds__(256) void k_sel_init(SelState *st, int64_t rank) {
-    st->hist[threadIdx.x] = 0;
+    for (int b = threadIdx.x; b < SEL_BINS; b += 256) st->hist[b] = 0;
     if (threadIdx.x == 0) {
         st->prefix = 0;
         st->mask = 0;
         st->rank = rank;
+        st->finished = 0;
     }
 }
 
-__global__ __launch_bounds__(256) void k_sel_hist(const double *vals, const int32_t *skip_if_neg, int64_t n,
-                                                  int shift, SelState *st) {
-    __shared__ int32_t cnt[256];
-    cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t prefix = st->prefix, mask = st->mask;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        if (skip_if_neg && skip_if_neg[i] < 0) continue;
-        uint64_t b = (uint64_t)__double_as_longlong(vals[i]);
-        if ((b & mask) == prefix) atomicAdd(&cnt[(b >> shift) & 0xFF], 1);
-    }
-    __syncthreads();
-    if (cnt[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], cnt[threadIdx.x]);
+__device__ inline bool sel_value(const double *vals, const int32_t *skip_if_neg, int64_t i, uint64_t *b) {
+    if (skip_if_neg && skip_if_neg[i] < 0) return false;
+    *b = (uint64_t)__double_as_longlong(vals[i]);
+    return true;
 }
 
-__global__ __launch_bounds__(256) void k_sel_pick(SelState *st, int shift, double *out, int last) {
+__global__ __launch_bounds__(256) void k_sel_round(const double *vals, const int32_t *skip_if_neg, int64_t n,
+                                                   int round, SelState *st, double *out) {
+    __shared__ int32_t cnt[SEL_BINS];
+    __shared__ int s_last;
+    int shift, bits;
+    sel_digit(round, shift, bits);
+    for (int b = threadIdx.x; b < SEL_BINS; b += 256) cnt[b] = 0;
+    __syncthreads();
+    const uint64_t prefix = st->prefix, mask = st->mask, dm = (1ull << bits) - 1;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        uint64_t b;
+        if (sel_value(vals, skip_if_neg, i, &b) && (b & mask) == prefix) atomicAdd(&cnt[(b >> shift) & dm], 1);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < SEL_BINS; b += 256)
+        if (cnt[b]) atomicAdd(&st->hist[b], cnt[b]);
+    __threadfence();  // this workgroup's counts before its arrival
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&st->finished, 1) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    for (int b = threadIdx.x; b < SEL_BINS; b += 256) {
+        cnt[b] = __hip_atomic_load(&st->hist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        st->hist[b] = 0;
+    }
+    __syncthreads();
+    int64_t r;
+    const int digit = sel_pick(cnt, st->rank, &r);
     if (threadIdx.x == 0) {
-        int64_t r = st->rank;
-        int digit = 255;
-        for (int g = 0; g < 256; ++g) {
-            if (r < st->hist[g]) { digit = g; break; }
-            r -= st->hist[g];
-        }
         st->rank = r;
-        st->prefix |= (uint64_t)digit << shift;
-        st->mask |= (uint64_t)0xFF << shift;
-        if (last) *out = __longlong_as_double((long long)st->prefix);
+        st->prefix = prefix | (uint64_t)digit << shift;
+        st->mask = mask | dm << shift;
+        st->finished = 0;
+        if (round + 1 == SEL_ROUNDS) *out = __longlong_as_double((long long)(prefix | (uint64_t)digit << shift));
     }
-    __syncthreads();
-    st->hist[threadIdx.x] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_sel_small(const double *vals, const int32_t *skip_if_neg, int64_t n,
+                                                   int64_t rank, double *out) {
+    __shared__ int32_t cnt[SEL_BINS];
+    uint64_t prefix = 0, mask = 0;
+    for (int round = 0; round < SEL_ROUNDS; ++round) {
+        int shift, bits;
+        sel_digit(round, shift, bits);
+        const uint64_t dm = (1ull << bits) - 1;
+        for (int b = threadIdx.x; b < SEL_BINS; b += 256) cnt[b] = 0;
+        __syncthreads();
+#pragma unroll 8
+        for (int64_t i = threadIdx.x; i < n; i += 256) {
+            uint64_t b;
+            if (sel_value(vals, skip_if_neg, i, &b) && (b & mask) == prefix) atomicAdd(&cnt[(b >> shift) & dm], 1);
+        }
+        __syncthreads();
+        const int digit = sel_pick(cnt, rank, &rank);
+        prefix |= (uint64_t)digit << shift;
+        mask |= dm << shift;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *out = __longlong_as_double((long long)prefix);
 }
 
 size_t radix_select_scratch_bytes() { return align_up(sizeof(SelState), 256); }
 
 void radix_select_f64(const double *vals, const int32_t *skip_if_neg, int64_t n, int64_t rank, double *out,
                       void *scratch, hipStream_t s) {
+    if (n <= SEL_SMALL) {
+        hipLaunchKernelGGL(k_sel_small, dim3(1), dim3(256), 0, s, vals, skip_if_neg, n, rank, out);
+        LAUNCH_CHECK();
+        return;
+    }
     SelState *st = static_cast<SelState *>(scratch);
     hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, s, st, rank);
     LAUNCH_CHECK();
-    const unsigned g = grid_for(n, 256) < 1024 ? grid_for(n, 256) : 1024;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_sel_hist, dim3(g), dim3(256), 0, s, vals, skip_if_neg, n, shift, st);
-        LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, s, st, shift, out, shift == 0);
+    const unsigned g = std::min<unsigned>(grid_for(n, 1024), 256u);
+    for (int round = 0; round < SEL_ROUNDS; ++round) {
+        hipLaunchKernelGGL(k_sel_round, dim3(g), dim3(256), 0, s, vals, skip_if_neg, n, round, st, out);
         LAUNCH_CHECK();
     }
 }
