@@ -78,7 +78,7 @@ typedef int32_t iso_status;
 /* Bits of iso_mst's `flags` argument (0 = every shortcut allowed).  The tree is
  * the same with any of them: they only select which rounds may skip the full
  * screen and which screen precision may run. */
-#define ISO_MST_NO_LISTS 0x1    /* no neighbour lists from the second round    */
+#define ISO_MST_NO_LISTS 0x1    /* no neighbour lists                          */
 #define ISO_MST_NO_FINAL 0x2    /* no final round joining <= 64 components    */
 #define ISO_MST_NO_ESCALATE 0x4 /* keep the requested screen precision even
                                    when its bound is too loose for the data  */
@@ -104,8 +104,8 @@ typedef int32_t iso_status;
 
 typedef struct {
     int32_t rounds;          /* Boruvka rounds                                   */
-    int32_t list_rounds;     /* rounds decided by the neighbour lists of the
-                                second round's screen instead of a full screen  */
+    int32_t list_rounds;     /* rounds decided by the neighbour lists of an
+                                earlier screen instead of a full screen         */
     int64_t candidates;      /* candidate pairs re-evaluated exactly (all rounds) */
     int64_t rescanned_rows;  /* rows whose candidate list overflowed and were
                                 re-evaluated against every other point          */
@@ -116,7 +116,8 @@ typedef struct {
                                 requested one, or ISO_PREC_FP32 when its error
                                 bound was too loose for the data (escalation)   */
     int32_t pair_bounds;     /* 1 when that screen used per-pair bounds        */
-    int64_t tile_pairs;      /* 256 x 256 tile pairs screened (all rounds)     */
+    int64_t tile_pairs;      /* 256 x 256 tile pairs screened (all rounds; not
+                                the sample that starts the neighbour lists)     */
     int64_t tile_pairs_full; /* tile pairs the same rounds would screen without
                                 the bounding-ball test (ISO_MST_NO_PRUNE)      */
 } iso_mst_info;
@@ -129,9 +130,10 @@ iso_status iso_mst_workspace_size(int64_t n, int64_t d, int32_t precision, size_
  * (Sec. 2.2 step 2 / Sec. 3.5).  The n x n distance matrix is never stored:
  * distances are formed tile by tile.  Edges are totally ordered by (D^2 under
  * `recheck`, smaller end id, larger end id), so the tree is unique.  Rounds
- * screen every inter-component pair, except that from the third round on a
- * round may be decided by the neighbour lists the second round's screen
- * builds, and once at most 64 components remain one final round joins them
+ * screen every inter-component pair, except that a round after the first may
+ * be decided by the neighbour lists that the first round's screen (or, for small
+ * n, loose bounds or without the bounding-ball test, the second's) builds, and
+ * once at most 64 components remain one final round joins them
  * all (both are switched off by ISO_MST_NO_LISTS / ISO_MST_NO_FINAL in
  * `flags`; the tree does not change).  Points are ordered into tiles of nearby
  * points, and a pair of tiles whose bounding balls are farther apart than any

@@ -49,7 +49,7 @@ def mst(points, precision: str = "fp32", recheck: str = "fp32", lists: bool = Tr
     ("fp32", "bf16", "fp8", or "int8" for 8-bit data); ``recheck`` the exact arithmetic that orders the edges
     ("fp32", or "fp64" for parity with the FP64 oracle).  ``lists`` and
     ``final_round`` allow the rounds that skip the full screen (neighbour lists
-    from the second round, one final round for the last <= 64 components); the
+    after the first round, one final round for the last <= 64 components); the
     tree is the same either way.  ``escalate`` lets a low-precision screen
     whose error bound is too loose for the data hand over to the FP32 screen
     (``info["screen_precision"]`` tells which one built the tree).

@@ -614,21 +614,50 @@ __global__ __launch_bounds__(256) void k_rescan(const float *__restrict__ X, int
 
 // ------------------------------------------------------------------ neighbour lists
 //
-// The tile-pair screen of the second round appends to each point i every
-// point j of another component with Dhat^2_ij <= tau_i = LIST_LAMBDA b_i, b_i
-// the point's first-round minimum (its nearest neighbour's Dhat^2).  Points
-// left out have Dhat^2_ij > tau_i, or >= the smallest dropped value once the
-// list was full, so t_i = min(tau_i, dropped) bounds every absent j from below:
-// D^2_ij >= t_i - E_ij >= t_i - Emax_i.  Components only merge, so a pair that
-// is absent because its points shared a component then stays irrelevant.  In a
-// later round a row is decided by its list when that lower bound exceeds the
-// recheck threshold the row's candidates are filtered with (min of
-// kappa (b + Emax) and the component bound U): every column that can still be
-// the row's or its component's lightest edge is then in the list, and the
-// row's list entries replace its screen.  Undecided rows are screened in the
-// gathered pass; when there are many, the round runs the full screen instead.
+// A tile-pair screen with lists appends to each point i every point j of
+// another component with Dhat^2_ij <= tau_i (pair bounds: with lower bound
+// lb_ij <= tau_i).  Points left out have a larger value, or one >= the smallest
+// dropped value once the list was full, so t_i = min(tau_i, dropped) bounds
+// every absent j from below: D^2_ij >= t_i - E_ij >= t_i - Emax_i (pair bounds,
+// and pairs of tiles that the ball test excluded: D^2_ij >= t_i).  Components
+// only merge, so a pair that is absent because its points shared a component
+// then stays irrelevant.  In a later round a row is decided by its list when
+// that lower bound exceeds the recheck threshold the row's candidates are
+// filtered with (min of kappa (b + Emax), pair bounds kappa ub, and the
+// component bound U): every column that can still be the row's or its
+// component's lightest edge is then in the list, and the row's list entries
+// replace its screen.  Undecided rows are screened in the gathered pass; when
+// there are many, the round runs the full screen instead.
+//
+// Which screen builds them.  Where the tile order puts near tiles first (the
+// pruned calls, 32 tiles and up) it is the first round's.  The diagonal tile
+// pairs, screened ahead, give each row minima over halves of its tile, the
+// largest of which becomes its first tau (k_list_tau).  The round's tile
+// pairs then run in shares that grow fourfold, and after each share a row that
+// lists more than LIST_KEEP entries lowers its tau to its LIST_KEEP-th value
+// and drops what is above (k_list_trim), so that a row appends some
+// 3 LIST_KEEP entries per share and ends with its nearest points whatever the
+// distances look like.  The eight nearest points leave no row undecided in the
+// second round and 2 % at most in the next two, on image-like, sparse, blob,
+// normal and mixture data, so no later round screens in full: n = 100,000,
+// d = 4096 sparse rows (pair bounds, which had no lists) went from five screens of
+// 26.7 ms to one, 157 -> 48.7 ms; n = 200,000, d = 784 from two to one,
+// 19.0 -> 17.0 ms.  Where the bound is too loose for lists on most rows (the
+// sample tells), below 32 tiles and with ISO_MST_NO_PRUNE (whose order has no
+// near tiles first) the second round's screen builds them, with
+// tau_i = LIST_LAMBDA b_i from the first round's minimum b_i (pair bounds: none).
 
 constexpr float LIST_LAMBDA = 1.1f;
+// The first round's lists, measured at n = 100,000, d = 4096 (sparse rows) and
+// n = 200,000, d = 784 (image-like), MST alone: LIST_KEEP 12 / 16 / 24: 53.0 / 49.6 /
+// 50.2 and 16.8 / 16.9 / 16.9 ms, 2,459 / 257 / 200 rows undecided in the sparse
+// rows' last round.  LIST_SLOTS 3 / 4 / 6, n = 50,000, d = 64 in clusters of 30 / of
+// 1,000: 12.5 / 11.7 / 11.9 and 6.3 / 6.5 / 7.5 ms.  LIST_FIRST 2 / 4 / 8 and growth
+// by 2 instead of 4 differ by less than 2 % on all of them.
+constexpr int LIST_SLOTS = 4;    // sampled minima per row
+constexpr int LIST_KEEP = 16;    // entries that set a row's next tau
+constexpr int LIST_MOST = 64;    // most entries a trimmed list keeps
+constexpr int LIST_FIRST = 2;    // the first share of the tile pairs, per tile (5 tiles seen by every row)
 constexpr double FR_EVAL_PER_POINT = 16.0;  // final round: most exact evaluations per point on average
 
 __global__ void k_list_init(const float *__restrict__ best, int64_t n, float *__restrict__ ltau,
@@ -636,38 +665,185 @@ __global__ void k_list_init(const float *__restrict__ best, int64_t n, float *__
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float b = best[i];
-    ltau[i] = b < SCR_INF ? b * LIST_LAMBDA : -1.0f;  // a point without a first-round minimum keeps no list
+    // a point without a first-round minimum keeps no list; finite, so that no
+    // padding (+inf) is listed
+    ltau[i] = b < SCR_INF ? fminf(b * LIST_LAMBDA, FLT_MAX) : -1.0f;
     lcnt[i] = 0;
     ldrop[i] = 0x7F800000u;
 }
 
+// The sample's labels: slot q of position pos holds bit q of pos, so that the
+// diagonal tile pairs, which skip pairs of equal labels, give each row its
+// minimum over the half of its tile with the other bit.
+__global__ void k_sample_labels(int64_t npos, int32_t *__restrict__ out) {
+    const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (pos >= npos) return;
+#pragma unroll
+    for (int q = 0; q < LIST_SLOTS; ++q) out[q * npos + pos] = (int32_t)(pos >> q & 1);
+}
+
+// First thresholds of the first round's lists, by position: tau is the largest
+// of the LIST_SLOTS sampled minima (slot q of position pos at
+// smp[q * npos + pos]; +inf, no point in that half, is left out), about the
+// third smallest value in the row's tile whatever the distances of other tiles
+// are, plus the margin 2 Emax that a row's decision needs (pair bounds: the
+// largest of the minima smp_ub of the upper bounds), up to a factor `margin`:
+// beyond it the bound is too loose for lists, and such a tau would list most
+// points of the first share.  Rows at that limit are counted in
+// counters[C_FORCE].  The least minimum starts the running one: it is the value
+// of a real pair.  (Minima over the tiles 1 .. 5 away instead of halves of the
+// own one, third smallest of six: where near tiles hold small clusters, tau
+// reached other clusters and lists overflowed; n = 50,000, d = 16 in clusters
+// of 300: 11.4 ms, 5.9 so, 7.1 with the second round's lists.)
+__global__ void k_list_tau(const int32_t *__restrict__ order, int64_t npos, int64_t n, const float *__restrict__ smp,
+                           const float *__restrict__ smp_ub, float margin, const float *__restrict__ pEmax,
+                           float *__restrict__ ltau, float *__restrict__ pltau, int32_t *__restrict__ lcnt,
+                           uint32_t *__restrict__ ldrop, float *__restrict__ pbest, float *__restrict__ pub,
+                           int32_t *__restrict__ counters) {
+    const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (pos >= npos) return;  // (whole tiles: no wave is cut)
+    const int32_t id = order[pos];
+    float lo = SCR_INF, lou = SCR_INF, top = -1.0f, topu = -1.0f;
+#pragma unroll
+    for (int q = 0; q < LIST_SLOTS; ++q) {
+        const float v = smp[q * npos + pos];
+        const float u = smp_ub ? smp_ub[q * npos + pos] : v;
+        lo = fminf(lo, v);
+        lou = fminf(lou, u);
+        if (v < SCR_INF) top = fmaxf(top, v);
+        if (u < SCR_INF) topu = fmaxf(topu, u);
+    }
+    pbest[pos] = lo;
+    if (smp_ub) pub[pos] = lou;
+    const float far = (smp_ub ? topu : top + 2.0f * pEmax[pos]) * (1.0f + 0x1p-10f);
+    // (finite: no padding, whose value is +inf, is listed; a row without a minimum keeps no list)
+    const float tau = id < n && top >= 0.0f ? fminf(fminf(far, top * margin), FLT_MAX) : -1.0f;
+    const int loose = __popcll(__ballot(tau >= 0.0f && far > top * margin));
+    if ((threadIdx.x & 63) == 0 && loose) atomicAdd(&counters[C_FORCE], loose);
+    pltau[pos] = tau;
+    if (id < n) {
+        ltau[id] = tau;
+        lcnt[id] = 0;
+        ldrop[id] = 0x7F800000u;
+    }
+}
+
+// Number of the wave's 2 x 64 values (unset: +inf bits and above) that are <= t.
+__device__ __forceinline__ int count_le(uint32_t a, uint32_t b, uint32_t t) {
+    return __popcll(__ballot(a <= t)) + __popcll(__ballot(b <= t));
+}
+
+// The k-th smallest of the wave's 2 x 64 nonnegative floats as bits (k >= 1,
+// at least k set): bit by bit from the top.
+__device__ __forceinline__ uint32_t kth_smallest(uint32_t a, uint32_t b, int k) {
+    uint32_t t = 0;
+#pragma unroll 1
+    for (int bit = 30; bit >= 0; --bit) {
+        const uint32_t c = t | (1u << bit);
+        if (count_le(a, b, c - 1u) < k) t = c;
+    }
+    return t;
+}
+
+// One wave per position: a list of more than LIST_KEEP entries is cut to those
+// at or below a lower tau: the LIST_KEEP-th smallest value plus the margin a
+// decision needs (2 Emax; pair bounds: the LIST_KEEP-th smallest upper bound
+// lb + 2 E_ij), but no more than LIST_MOST entries.
+__global__ __launch_bounds__(256) void k_list_trim(const int32_t *__restrict__ order, int64_t npos, int64_t n,
+                                                   const float *__restrict__ Emax, const float *__restrict__ rn,
+                                                   const float *__restrict__ re, ScreenBound bound, int pb,
+                                                   float *__restrict__ ltau, float *__restrict__ pltau,
+                                                   int32_t *__restrict__ lcnt, int32_t *__restrict__ lj,
+                                                   float *__restrict__ lv) {
+    static_assert(LIST_CAP == 128, "two entries per lane");
+    const int lane = threadIdx.x & 63;
+    for (int64_t pos = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); pos < npos; pos += (int64_t)gridDim.x * 4) {
+        const int64_t i = order[pos];
+        if (i >= n) continue;
+        const int cnt = min(lcnt[i], LIST_CAP);
+        if (cnt <= LIST_KEEP) continue;
+        int32_t j[2];
+        uint32_t v[2], u[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = 64 * h + lane;
+            const bool in = q < cnt;
+            j[h] = in ? lj[i * LIST_CAP + q] : 0;
+            const float f = in ? lv[i * LIST_CAP + q] : SCR_INF;
+            v[h] = __float_as_uint(f);
+            u[h] = v[h];
+            if (pb && in)
+                u[h] = __float_as_uint(fmaf(2.0f, pair_bound(bound, rn[i], rn[j[h]], re[i], re[j[h]]), f));
+        }
+        const float kth = __uint_as_float(kth_smallest(u[0], u[1], LIST_KEEP));
+        float tau = (pb ? kth : kth + 2.0f * Emax[i]) * (1.0f + 0x1p-10f);
+        if (count_le(v[0], v[1], __float_as_uint(tau)) > LIST_MOST)
+            tau = __uint_as_float(kth_smallest(v[0], v[1], LIST_MOST));
+        if (!(tau < ltau[i])) continue;
+        int kept = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool in = v[h] <= __float_as_uint(tau);
+            const unsigned long long bal = __ballot(in);
+            const int at = kept + __popcll(bal & ((1ull << lane) - 1ull));
+            if (in) {
+                lj[i * LIST_CAP + at] = j[h];
+                lv[i * LIST_CAP + at] = __uint_as_float(v[h]);
+            }
+            kept += __popcll(bal);
+        }
+        if (lane == 0) {
+            ltau[i] = tau;
+            pltau[pos] = tau;
+            lcnt[i] = kept;
+        }
+    }
+}
+
 // One wave per row: b_i = min over the list's entries in other components of
-// their Dhat^2 (an upper bound of the row's minimum; +inf without such entries).
+// their Dhat^2 (an upper bound of the row's minimum; +inf without such
+// entries).  With pair bounds (ub != nullptr) of their lower bounds, and ub_i
+// the least lb + 2 E_ij: lb = (Dhat^2 - E) less 2^-21 (Dhat^2 + E), or 0 when that
+// is negative, so Dhat^2 + E <= (lb + 2 E) (1 + 2^-20), and the 2^-18 covers
+// this evaluation's roundings too.
 __global__ __launch_bounds__(256) void k_list_best(int64_t n, const int32_t *__restrict__ comp,
                                                    const int32_t *__restrict__ lcnt, const int32_t *__restrict__ lj,
-                                                   const float *__restrict__ lv, float *__restrict__ best) {
+                                                   const float *__restrict__ lv, const float *__restrict__ rn,
+                                                   const float *__restrict__ re, ScreenBound bound,
+                                                   float *__restrict__ best, float *__restrict__ ub) {
     const int lane = threadIdx.x & 63;
     for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
         const int ci = comp[i];
         const int cnt = min(lcnt[i], LIST_CAP);
-        uint32_t m = 0x7F800000u;
+        uint32_t m = 0x7F800000u, mu = 0x7F800000u;
         for (int q = lane; q < cnt; q += 64) {
             const int32_t j = lj[i * LIST_CAP + q];
-            if (comp[j] != ci) m = min(m, __float_as_uint(lv[i * LIST_CAP + q]));
+            if (comp[j] == ci) continue;
+            const float v = lv[i * LIST_CAP + q];
+            m = min(m, __float_as_uint(v));
+            if (ub) {
+                const float E = pair_bound(bound, rn[i], rn[j], re[i], re[j]);
+                mu = min(mu, __float_as_uint(fmaf(2.0f, E, v) * (1.0f + 0x1p-18f)));
+            }
         }
         m = wave_min_u32(m);
-        if (lane == 0) best[i] = __uint_as_float(m);
+        if (ub) mu = wave_min_u32(mu);
+        if (lane == 0) {
+            best[i] = __uint_as_float(m);
+            if (ub) ub[i] = __uint_as_float(mu);
+        }
     }
 }
 
 // One wave per row: decide the row from its list (candidates into cj/cl as
 // the screen would leave them, ccnt > SCR_CAP on overflow) or mark it
-// SCR_FORCE for the gathered pass.
+// SCR_FORCE for the gathered pass.  (With pair bounds, ub != nullptr, the list's
+// values are lower bounds already.)
 __global__ __launch_bounds__(256) void k_list_capture(
     int64_t n, const int32_t *__restrict__ comp, const uint32_t *__restrict__ comp_ub, const float *__restrict__ best,
-    const float *__restrict__ Emax, const float *__restrict__ rn, const float *__restrict__ re, ScreenBound bound,
-    const float *__restrict__ ltau, const int32_t *__restrict__ lcnt, const uint32_t *__restrict__ ldrop,
-    const int32_t *__restrict__ lj, const float *__restrict__ lv, float kappa, float dn, int32_t *__restrict__ ccnt,
+    const float *__restrict__ ub, const float *__restrict__ Emax, const float *__restrict__ rn,
+    const float *__restrict__ re, ScreenBound bound, const float *__restrict__ ltau, const int32_t *__restrict__ lcnt,
+    const uint32_t *__restrict__ ldrop, const int32_t *__restrict__ lj, const float *__restrict__ lv, float kappa, float dn, int32_t *__restrict__ ccnt,
     int32_t *__restrict__ cj, float *__restrict__ cl, int32_t *__restrict__ counters) {
     const int lane = threadIdx.x & 63;
     for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
@@ -675,9 +851,9 @@ __global__ __launch_bounds__(256) void k_list_capture(
         const float b = best[i], E = Emax[i];
         const uint32_t ubits = comp_ub[ci];
         const float U = ubits == U32_MAX ? SCR_INF : __uint_as_float(ubits) * dn;
-        const float thr = fminf(b < SCR_INF ? (b + E) * kappa : SCR_INF, U);
+        const float thr = fminf(b < SCR_INF ? (ub ? ub[i] : b + E) * kappa : SCR_INF, U);
         const float t = fminf(ltau[i], __uint_as_float(ldrop[i]));
-        if (!(thr < SCR_INF) || !(lower_of(t, E) > thr)) {
+        if (!(thr < SCR_INF) || !((ub ? t : lower_of(t, E)) > thr)) {
             if (lane == 0) {
                 ccnt[i] = SCR_FORCE;
                 atomicAdd(&counters[C_FORCE], 1);
@@ -695,7 +871,8 @@ __global__ __launch_bounds__(256) void k_list_capture(
             if (q < cnt) {
                 j = lj[i * LIST_CAP + q];
                 if (comp[j] != ci) {
-                    L = lower_of(lv[i * LIST_CAP + q], pair_bound(bound, ri, rn[j], ei, re[j]));
+                    L = lv[i * LIST_CAP + q];
+                    if (!ub) L = lower_of(L, pair_bound(bound, ri, rn[j], ei, re[j]));
                     keep = L <= thr;
                 }
             }
@@ -1842,7 +2019,7 @@ __global__ __launch_bounds__(256) void k_tile_reach(const float *__restrict__ pb
         r = fminf(r, __uint_as_float(comp_ub[c]) * dn);
         if (pltau) {
             const float tau = pltau[pos];
-            if (tau >= 0.0f) r = fmaxf(r, (tau + pEmax[pos]) * THR_UP);
+            if (tau >= 0.0f) r = fmaxf(r, tau * THR_UP);
         }
         m = fmaxf(m, r);
     }
@@ -2488,10 +2665,11 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
 
     int64_t ncomp = n;
     int rounds = 0, list_rounds = 0, final_components = 0;
-    // (the neighbour lists and the final round decide with the separable
-    // bound, which pair-bound data makes useless: every round is screened)
+    // (LISTS_BUILDING: by the coming screen, the first round's where tiles are
+    // in a near order.  Pair-bound data keeps lists only there; the final round
+    // decides with the separable bound, which such data makes useless.)
     enum { LISTS_NONE, LISTS_BUILDING, LISTS_READY, LISTS_OFF } lists =
-        ((P.options & ISO_MST_NO_LISTS) || pb) ? LISTS_OFF : LISTS_NONE;
+        (P.options & ISO_MST_NO_LISTS) || (pb && !prune) ? LISTS_OFF : prune ? LISTS_BUILDING : LISTS_NONE;
     bool final_off = (P.options & ISO_MST_NO_FINAL) != 0 || pb;
     SA.ub = ubp;
     SA.psq = P.psq;
@@ -2643,6 +2821,48 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
         return {(int64_t)hk[0], (int64_t)hk[1]};
     };
     EventPair scr2(timed);
+
+    // The thresholds of the first round's lists (k_list_tau), from LIST_SLOTS
+    // screens of the diagonal tile pairs, whose labels and minima go to the
+    // list arrays, not yet in use.  False, and no lists, where the bound is too
+    // loose for most rows.
+    auto sample_lists = [&]() -> bool {
+        static_assert((1 << LIST_SLOTS) <= GT && 2 * LIST_SLOTS < LIST_CAP, "sampled minima");
+        float *const smp = P.lv, *const smp_ub = pb ? P.lv + LIST_SLOTS * P.n_pad : nullptr;
+        ISO_REQUIRE((pb ? 2 : 1) * LIST_SLOTS * P.n_pad <= LIST_CAP * n, ISO_ERR_INTERNAL, "sampled minima");
+        fill<uint32_t>(reinterpret_cast<uint32_t *>(smp), 0x7F800000u, (pb ? 2 : 1) * LIST_SLOTS * P.n_pad, s);
+        hipLaunchKernelGGL(k_sample_labels, dim3(grid_for(P.n_pad, 256)), dim3(256), 0, s, P.n_pad, P.lj);
+        LAUNCH_CHECK();
+        fill<int32_t>(P.ccnt, 0, n, s);
+        fill<int32_t>(P.counters + C_FORCE, 0, 1, s);
+        // only minima are wanted: with a negative kappa nothing passes the
+        // capture thresholds (b + E) kappa
+        const float with = SA.kappa;
+        SA.kappa = -1.0f;
+        for (int q = 0; q < LIST_SLOTS; ++q) {
+            SA.pcomp = P.lj + q * P.n_pad;
+            SA.pbest = smp + q * P.n_pad;
+            if (pb) SA.pub = smp_ub + q * P.n_pad;
+            launch_screen_pairs(SA, P.pairs, P.nt, 0, s);
+        }
+        SA.pcomp = P.pcomp;
+        SA.kappa = with;
+        SA.pbest = P.pbest;
+        SA.pub = pb ? P.pub : nullptr;
+        hipLaunchKernelGGL(k_list_tau, dim3(grid_for(P.n_pad, 256)), dim3(256), 0, s, P.perm, P.n_pad, n, smp, smp_ub,
+                           1.0f + std::max(1.0f / 32.0f, 6.0f / (float)d), P.pEmax, P.ltau, P.pltau, P.lscnt, P.ldrop, P.pbest, P.pub, P.counters);
+        LAUNCH_CHECK();
+        int32_t loose = 0;
+        R.get(&loose, P.counters + C_FORCE, sizeof(int32_t), s);
+        R.sync(s);
+        if (2 * (int64_t)loose > n) return false;
+        SA.ltau = P.ltau;
+        SA.lcnt = P.lscnt;
+        SA.ldrop = P.ldrop;
+        SA.lj = P.lj;
+        SA.lv = P.lv;
+        return true;
+    };
 
     // The final round (at most FR_KC components left): true when it joined
     // them all, false when a point's candidate list overflowed (the round is
@@ -2877,12 +3097,12 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
             }
             final_off = true;  // a candidate list overflowed: this and later rounds screen the plain way
         }
-        // From the third round on, rows are first decided by their neighbour
-        // lists; the round screens only when too many rows stay undecided.
+        // Once there are lists, rows are first decided by them; the round
+        // screens only when too many rows stay undecided.
         bool list_round = false;
         if (lists == LISTS_READY) {
-            hipLaunchKernelGGL(k_list_best, dim3(row_grid(n)), dim3(256), 0, s, n, P.comp, P.lscnt, P.lj, P.lv,
-                               P.best);
+            hipLaunchKernelGGL(k_list_best, dim3(row_grid(n)), dim3(256), 0, s, n, P.comp, P.lscnt, P.lj, P.lv, P.rn,
+                               P.re, bound, P.best, ubp);
             LAUNCH_CHECK();
             fill<uint32_t>(P.comp_ub, U32_MAX, ncomp, s);
             hipLaunchKernelGGL(k_comp_ub, dim3(grid_for(P.n_pad, 256)), dim3(256), 0, s, P.perm, P.n_pad, P.best,
@@ -2890,7 +3110,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
             LAUNCH_CHECK();
             fill<int32_t>(P.counters + C_FORCE, 0, 1, s);
             hipLaunchKernelGGL(k_list_capture, dim3(row_grid(n)), dim3(256), 0, s, n, P.comp, P.comp_ub, P.best,
-                               P.Emax, P.rn, P.re, bound, P.ltau, P.lscnt, P.ldrop, P.lj, P.lv, kappa, dn, P.ccnt, P.cj,
+                               ubp, P.Emax, P.rn, P.re, bound, P.ltau, P.lscnt, P.ldrop, P.lj, P.lv, kappa, dn, P.ccnt, P.cj,
                                P.cl, P.counters);
             LAUNCH_CHECK();
             int32_t h_force = 0;
@@ -2953,14 +3173,40 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
                 SA.lv = P.lv;
                 lists = LISTS_BUILDING;
             }
+            bool first_lists = lists == LISTS_BUILDING && rounds == 1;
             pos_gather(P.perm, P.n_pad, SA.lcnt != nullptr);
-            fill<uint32_t>(reinterpret_cast<uint32_t *>(P.pbest), 0x7F800000u, P.n_pad, s);  // +inf
-            if (ubp) fill<uint32_t>(reinterpret_cast<uint32_t *>(P.pub), 0x7F800000u, P.n_pad, s);
-            fill<int32_t>(P.ccnt, 0, n, s);
+            if (!first_lists) {
+                fill<uint32_t>(reinterpret_cast<uint32_t *>(P.pbest), 0x7F800000u, P.n_pad, s);  // +inf
+                if (ubp) fill<uint32_t>(reinterpret_cast<uint32_t *>(P.pub), 0x7F800000u, P.n_pad, s);
+            }
             SA.rows = nullptr;
             SA.nrows = 0;
             scr.start(s);
-            launch_screen_pairs(SA, pairs_use, nmask, noff, s);
+            if (first_lists && !sample_lists()) {
+                // (the sample's minima, of real pairs, stay as the running ones)
+                first_lists = false;
+                lists = pb ? LISTS_OFF : LISTS_NONE;
+            }
+            fill<int32_t>(P.ccnt, 0, n, s);
+            if (first_lists) {
+                // shares of the tile pairs, each four times what went before; the
+                // masked pairs go with the first one
+                int64_t at = 0, end = std::min<int64_t>(LIST_FIRST * P.nt, noff);
+                auto share = [&](int64_t masked) {
+                    launch_screen_pairs(SA, masked ? pairs_use : pairs_use + nmask + at, masked, end - at, s);
+                    hipLaunchKernelGGL(k_list_trim, dim3(row_grid(P.n_pad)), dim3(256), 0, s, P.perm, P.n_pad, n, P.Emax,
+                                       P.rn, P.re, bound, pb ? 1 : 0, P.ltau, P.pltau, P.lscnt, P.lj, P.lv);
+                    LAUNCH_CHECK();
+                };
+                share(nmask);
+                while (end < noff) {
+                    at = end;
+                    end = 32 * at > 7 * noff ? noff : 4 * at;
+                    share(0);
+                }
+            } else {
+                launch_screen_pairs(SA, pairs_use, nmask, noff, s);
+            }
             scr.stop(s);
             if (want_q) build_q();
             if (prune) {

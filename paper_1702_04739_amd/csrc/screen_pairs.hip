@@ -124,10 +124,11 @@ struct PairLDS {
     uint32_t umin;             // final round: the item's bound of its pair of components' lightest edge
 };
 
-// Pair bounds (BF16 plain rounds with A.ub set): per element its own bound
+// Pair bounds (BF16 rounds with A.ub set): per element its own bound
 // E_ij, the tile minima of Dhat^2 + E_ij (upper bounds) and of the lower bound
 // Dhat^2 - E_ij, and the columns' norm and representation-error bounds; kept in
-// the list-staging half of the epilogue buffer, which plain rounds leave idle.
+// the list-staging half of the epilogue buffer, which is not written before the
+// barrier that follows their last use.
 struct PBLDS {
     uint32_t rminU[PT], rminL[PT];
     uint32_t cminU[PH], cminL[PH];
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_screen_pairs(ScreenArgs A, const
                                                             int64_t per_xcd, int64_t nitems) {
     constexpr bool LIST = MODE == MODE_LIST, FINAL = MODE == MODE_FINAL;
     static_assert(!(FINAL && MASKED), "the final round pairs tiles of different components only");
-    static_assert(!PB || (MODE == MODE_PLAIN && REP == ISO_PREC_BF16), "pair bounds: BF16 plain rounds only");
+    static_assert(!PB || (!FINAL && REP == ISO_PREC_BF16), "pair bounds: BF16, no final round");
     using P = PPrec<REP>;
     using T = typename P::T;
     using WL = PWave<REP>;
@@ -799,14 +800,18 @@ __global__ __launch_bounds__(64 * NW, 2) void k_screen_pairs(ScreenArgs A, const
             const float curu = p < A.n ? __uint_as_float(min(oldu, mU)) : SCR_INF;
             const float thr = curu * A.kappa;  // (the staged values are already lower bounds)
             const bool hotu = p < A.n && mL < INF_BITS && __uint_as_float(mL) <= thr;
+            // (the lists of pair-bound data hold lower bounds)
+            const bool lst = LIST && p < A.n && mL < INF_BITS && __uint_as_float(mL) <= pre_tau[e];
             if (is_row) {
                 S.rmin[t] = __float_as_uint(thr);
                 S.rE[t] = 0.0f;
-                S.rhot[t] = hotu ? 1 : 0;
+                S.rhot[t] = (hotu ? 1 : 0) | (lst ? 2 : 0);
             } else {
                 S.cmin[t] = __float_as_uint(thr);
                 S.cE[t] = 0.0f;
                 if (hotu) atomicOr(&S.chot[t >> 5], 1u << (t & 31));
+                if (lst) atomicOr(&S.clst[t >> 5], 1u << (t & 31));
+                if constexpr (LIST) S.csq[t] = lst ? pre_tau[e] : -SCR_INF;
             }
             continue;
         }
@@ -1106,19 +1111,23 @@ void launch_pairs(const ScreenArgs &A, const int2 *pairs, int64_t nmask, int64_t
     auto grid = [](int64_t per_xcd) { return dim3((unsigned)(8 * per_xcd)); };
     const bool list = A.lcnt != nullptr, final_round = A.bestc != nullptr, pb = A.ub != nullptr;
     ISO_REQUIRE(!(final_round && (list || nmask > 0)), ISO_ERR_INTERNAL, "final round with lists or masked pairs");
-    ISO_REQUIRE(!pb || (REP == ISO_PREC_BF16 && !list && !final_round), ISO_ERR_INTERNAL,
-                "pair bounds only in plain BF16 rounds");
+    ISO_REQUIRE(!pb || (REP == ISO_PREC_BF16 && !final_round), ISO_ERR_INTERNAL,
+                "pair bounds only in BF16 rounds before the final one");
+    constexpr bool BF = REP == ISO_PREC_BF16;
     // the unmasked tile pairs, two halves each ...
     if (noff > 0) {
         const int64_t items = 2 * noff, per_xcd = (items + 7) / 8;
         if (final_round)
             hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_FINAL>), grid(per_xcd), block, 0, s, A, pairs + nmask,
                                per_xcd, items);
+        else if (list && pb)
+            hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_LIST, BF>), grid(per_xcd), block, 0, s, A,
+                               pairs + nmask, per_xcd, items);
         else if (list)
             hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_LIST>), grid(per_xcd), block, 0, s, A, pairs + nmask,
                                per_xcd, items);
         else if (pb)
-            hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_PLAIN, REP == ISO_PREC_BF16>), grid(per_xcd), block, 0,
+            hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_PLAIN, BF>), grid(per_xcd), block, 0,
                                s, A, pairs + nmask, per_xcd, items);
         else
             hipLaunchKernelGGL((k_screen_pairs<REP, false, MODE_PLAIN>), grid(per_xcd), block, 0, s, A, pairs + nmask,
@@ -1130,11 +1139,14 @@ void launch_pairs(const ScreenArgs &A, const int2 *pairs, int64_t nmask, int64_t
     // running minima are already low, so that few of its rows are flagged
     if (nmask > 0) {
         const int64_t items = 2 * nmask, per_xcd = (items + 7) / 8;
-        if (list)
+        if (list && pb)
+            hipLaunchKernelGGL((k_screen_pairs<REP, true, MODE_LIST, BF>), grid(per_xcd), block, 0, s, A,
+                               pairs, per_xcd, items);
+        else if (list)
             hipLaunchKernelGGL((k_screen_pairs<REP, true, MODE_LIST>), grid(per_xcd), block, 0, s, A, pairs, per_xcd,
                                items);
         else if (pb)
-            hipLaunchKernelGGL((k_screen_pairs<REP, true, MODE_PLAIN, REP == ISO_PREC_BF16>), grid(per_xcd), block, 0,
+            hipLaunchKernelGGL((k_screen_pairs<REP, true, MODE_PLAIN, BF>), grid(per_xcd), block, 0,
                                s, A, pairs, per_xcd, items);
         else
             hipLaunchKernelGGL((k_screen_pairs<REP, true, MODE_PLAIN>), grid(per_xcd), block, 0, s, A, pairs, per_xcd,
