@@ -111,7 +111,8 @@ typedef struct {
                                 re-evaluated against every other point          */
     double mst_weight;       /* sum of the n-1 FP64 edge lengths                 */
     int32_t final_components;/* components joined at once by the final round
-                                (0: the last round was a plain round)           */
+                                (0: the last round was a plain round), or by the
+                                last round on the matrix of exact distances     */
     int32_t screen_precision;/* precision of the screen that built the tree: the
                                 requested one, or ISO_PREC_FP32 when its error
                                 bound was too loose for the data (escalation)   */
@@ -139,7 +140,9 @@ iso_status iso_mst_workspace_size(int64_t n, int64_t d, int32_t precision, size_
  * points, and a pair of tiles whose bounding balls are farther apart than any
  * of their points' current lightest-edge bound is not screened (the
  * bounding-ball test of dual-tree Boruvka; ISO_MST_NO_PRUNE turns it off; the
- * tree does not change).
+ * tree does not change).  With an FP32 screen and no flags up to 4,096 points
+ * take no screen: the rounds run on the matrix of all exact distances (info:
+ * no tile pairs, n (n - 1) / 2 candidates).
  *   X       [n*ld] FP32 points (read only).
  *   precision  ISO_PREC_* of the screen;  recheck  ISO_RECHECK_* (edge order);
  *   flags   OR of ISO_MST_NO_* bits, or 0.

@@ -33,6 +33,7 @@
 #include <utility>
 #include <vector>
 
+#include "dense.hpp"
 #include "screen.hpp"
 
 namespace iso {
@@ -3431,6 +3432,88 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     }
 }
 
+// The tree of few points from all their exact distances: up to DENSE_MAX_N
+// points (16-bit ids, the join's and the rooting's tables in LDS) and
+// DENSE_MAX_WORK coordinate differences, and only where the call leaves
+// everything to the library: a screen precision other than FP32 and any flag
+// ask for the screened rounds.  Both sides, FP32 recheck, us: n = 150, d = 5: 142
+// and 746; n = 2048, d = 16: 270 and 1128; n = 4096, d = 16 / 784 / 4096: 563 and
+// 1299 / 1396 and 2112 / 4526 and 6888 (FP64 recheck 8611 and 8679, where the work
+// limit lies).
+constexpr double DENSE_MAX_WORK = 0x1p36;
+
+struct DensePlan {
+    DenseArgs A;
+    double *elen = nullptr;
+    char *out = nullptr;  // DenseState, then the sum of the lengths
+    void carve(Arena &a, int64_t n, bool f64) {
+        A.n = n;
+        A.f64 = f64;
+        out = a.take<char>(OUT_BYTES);
+        A.st = reinterpret_cast<DenseState *>(out);
+        A.comp = a.take<int32_t>(n);
+        A.eu = a.take<int32_t>(n);
+        A.ev = a.take<int32_t>(n);
+        elen = a.take<double>(n);
+        A.buf = a.take<char>(dense_bytes(n, f64));
+    }
+    static constexpr size_t OUT_BYTES = 32;
+    static_assert(sizeof(DenseState) <= OUT_BYTES - sizeof(double), "state and sum");
+};
+
+bool dense_calls(int64_t n, int64_t d, int32_t precision, uint32_t flags) {
+    return precision == ISO_PREC_FP32 && flags == 0 && n <= DENSE_MAX_N && (double)n * (double)n * (double)d <= DENSE_MAX_WORK;
+}
+
+size_t dense_plan_bytes(int64_t n, bool f64) {
+    Arena a;
+    DensePlan p;
+    p.carve(a, n, f64);
+    return a.used;
+}
+
+// False, and nothing returned, where a distance is out of the range that the
+// screen's own checks allow for (or not a number): the screened rounds decide.
+bool dense_mst(const float *X, int64_t n, int64_t d, int64_t ld, bool f64, int32_t *parent, double *length,
+               iso_mst_info *info, Arena &arena, hipStream_t s) {
+    const bool timed = timing().enabled != 0;
+    EventPair whole(timed);
+    whole.start(s);
+    DensePlan P;
+    P.carve(arena, n, f64);
+    P.A.X = X;
+    P.A.d = d;
+    P.A.ld = ld;
+    const int64_t m = n - 1;
+    double *const wsum = reinterpret_cast<double *>(P.out + DensePlan::OUT_BYTES - sizeof(double));
+    launch_dense_tree(P.A, s);
+    hipLaunchKernelGGL(k_refine, dim3(grid_for(m, 256)), dim3(256), 0, s, X, d, ld, P.A.eu, P.A.ev, m, P.elen);
+    LAUNCH_CHECK();
+    launch_dense_root(P.A, P.elen, parent, length, s);
+    hipLaunchKernelGGL(k_sum_lengths, dim3(1), dim3(1024), 0, s, length, n, wsum);
+    LAUNCH_CHECK();
+    char h[DensePlan::OUT_BYTES];
+    HIP_CHECK(hipMemcpyAsync(h, P.out, sizeof(h), hipMemcpyDeviceToHost, s));
+    whole.stop(s);
+    HIP_CHECK(hipStreamSynchronize(s));
+    DenseState st;
+    std::memcpy(&st, h, sizeof(st));
+    if (timed) {
+        timing().mst_calls += st.bad ? 0 : 1;
+        timing().mst_ms += whole.elapsed_ms();
+    }
+    if (st.bad || st.ncomp != 1) return false;
+    if (info) {
+        *info = iso_mst_info{};
+        info->rounds = st.rounds;
+        info->final_components = st.joined;
+        info->candidates = n * m / 2;
+        info->screen_precision = ISO_PREC_FP32;
+        std::memcpy(&info->mst_weight, h + sizeof(h) - sizeof(double), sizeof(double));
+    }
+    return true;
+}
+
 }  // namespace
 
 }  // namespace iso
@@ -3447,6 +3530,7 @@ extern "C" iso_status iso_mst_workspace_size(int64_t n, int64_t d, int32_t preci
                     ISO_ERR_INVALID_ARG, "unknown precision %d", precision);
         // room for the FP32 screen too (a screen whose bound is too loose escalates to it)
         *bytes = std::max(plan_bytes(make_plan(n, d, d, precision)), plan_bytes(make_plan(n, d, d, ISO_PREC_FP32)));
+        if (dense_calls(n, d, precision, 0)) *bytes = std::max(*bytes, dense_plan_bytes(n, true));
     });
 }
 
@@ -3472,14 +3556,21 @@ extern "C" iso_status iso_mst(const float *X, int64_t n, int64_t d, int64_t ld, 
         MstPlan P = make_plan(n, d, ld, precision);
         P.options = options;
         const size_t need = std::max(plan_bytes(P), plan_bytes(make_plan(n, d, ld, ISO_PREC_FP32)));
+        const bool f64 = recheck == ISO_RECHECK_FP64;
+        const size_t dense = dense_calls(n, d, precision, flags) ? dense_plan_bytes(n, f64) : 0;
         ScopedWorkspace owned;
         if (ws == nullptr) {
             owned.stream = s;
-            HIP_CHECK(hipMallocAsync(&owned.ptr, need, s));
+            ws_bytes = std::max(need, dense);
+            HIP_CHECK(hipMallocAsync(&owned.ptr, ws_bytes, s));
             ws = owned.ptr;
-            ws_bytes = need;
         }
         ISO_REQUIRE(ws_bytes >= need, ISO_ERR_WORKSPACE, "workspace %zu bytes < required %zu", ws_bytes, need);
+        // (a workspace that holds the screened rounds only gets them)
+        if (dense > 0 && ws_bytes >= dense) {
+            Arena a{static_cast<char *>(ws), 0, ws_bytes};
+            if (dense_mst(X, n, d, ld, f64, parent, length, info, a, s)) return;
+        }
         Arena a{static_cast<char *>(ws), 0, ws_bytes};
         P.carve(a);
         bool escalate = false;
