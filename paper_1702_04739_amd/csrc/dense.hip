@@ -9,8 +9,8 @@
 // matrix that stays in the last-level cache; each Boruvka round is one launch
 // over its rows, whose last workgroup joins the components, and one workgroup
 // roots the tree.  The edge order is that of the rechecked screen, (D^2, smaller
-// id, larger id), and so is the tree.  No host wait before the end.  0.14 and
-// 0.27 ms on those two, half of it the launches.
+// id, larger id), and so is the tree.  No host wait before the end.  0.12 and
+// 0.15 ms on those two, half of it the launches.
 #include <cmath>
 
 #include "common.hpp"
@@ -31,8 +31,9 @@ __device__ __forceinline__ bool too_big(T v) {
 
 // Writes a 64 x 64 tile and, off the diagonal, its transpose (through LDS, so
 // that both are whole rows); thread (lane, w) holds rows 16 w + r, column lane.
+// The columns n .. nd - 1 that pad a row to whole 16 bytes are +inf.
 template <class T>
-__device__ __forceinline__ void put_tile(T (&t)[DT][DT + 1], const T (&v)[16], int64_t n, int64_t I0, int64_t J0,
+__device__ __forceinline__ void put_tile(T (&t)[DT][DT + 1], const T (&v)[16], int64_t n, int64_t nd, int64_t I0, int64_t J0,
                                          T *__restrict__ D) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const T inf = (T)__builtin_huge_val();
@@ -40,7 +41,7 @@ __device__ __forceinline__ void put_tile(T (&t)[DT][DT + 1], const T (&v)[16], i
     for (int r = 0; r < 16; ++r) {
         const int64_t i = I0 + 16 * w + r, j = J0 + lane;
         const T d2 = i == j ? inf : v[r];
-        if (i < n && j < n) D[i * n + j] = d2;
+        if (i < n && j < nd) D[i * nd + j] = j < n ? d2 : inf;
         t[16 * w + r][lane] = d2;
     }
     if (I0 == J0) return;
@@ -48,64 +49,110 @@ __device__ __forceinline__ void put_tile(T (&t)[DT][DT + 1], const T (&v)[16], i
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int64_t j = J0 + 16 * w + r, i = I0 + lane;
-        if (i < n && j < n) D[j * n + i] = t[lane][16 * w + r];
+        if (i < n && j < n) D[j * nd + i] = t[lane][16 * w + r];
     }
 }
 
-// FP32 distances, d <= 64: one thread per pair holds the 64 partial sums that
-// the lanes of a wave hold in the recheck (one square each here, 0 past d) and
-// adds them in its butterfly's order.  Bound by those 63 additions; a wave per
-// pair would spend six cross-lane steps on each.
+// Rows I0 .. I0 + 63 of X, coordinates c .. c + W - 1 (0 past the end), as
+// xi[row][coordinate] or transposed: lane = coordinate, a wave takes every
+// fourth row (64 / W of them at once), and every load is issued before the first
+// is used.
+template <int W, class Put>
+__device__ __forceinline__ void load_rows(const float *__restrict__ X, int64_t n, int64_t d, int64_t ld, int64_t I0,
+                                          int64_t c, Put put) {
+    constexpr int PER = 64 / W, STEPS = DT / (4 * PER);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int t = lane & (W - 1), sub = lane / W;
+    float v[STEPS];
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q) {
+        const int64_t r = I0 + (q * 4 + w) * PER + sub;
+        v[q] = X[min(r, n - 1) * ld + min(c + t, d - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q) {
+        const int r = (q * 4 + w) * PER + sub;
+        put(r, t, I0 + r < n && c + t < d ? v[q] : 0.0f);
+    }
+}
+
+// FP32 distances, d <= W <= 64: one thread per pair holds the partial sums that
+// the lanes of a wave hold in the recheck (one square each here) and adds them
+// in its butterfly's order; the sums of the lanes past W, all 0, are left out.
+// Bound by those additions; a wave per pair would spend six cross-lane steps on
+// each.  n = 2000, d = 16: 16 us (35
+// with all 64 sums and the rows loaded one by one).
+template <int W>
 __global__ __launch_bounds__(256) void k_dense_f32_low(const float *__restrict__ X, int64_t n, int64_t d, int64_t ld,
-                                                       float *__restrict__ D, DenseState *__restrict__ st) {
+                                                       int64_t nd, float *__restrict__ D, DenseState *__restrict__ st) {
     if (blockIdx.y < blockIdx.x) return;
-    __shared__ __attribute__((aligned(16))) float xi[DT][DT];
-    __shared__ float xj[DT][DT + 1];  // [coordinate][column]
+    __shared__ __attribute__((aligned(16))) float xi[DT][W];
+    __shared__ float xj[W][DT + 1];  // [coordinate][column]
     __shared__ float tile[DT][DT + 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t I0 = (int64_t)blockIdx.x * DT, J0 = (int64_t)blockIdx.y * DT;
-    for (int q = threadIdx.x; q < DT * DT; q += 256) {
-        const int r = q / DT, t = q % DT;
-        xi[r][t] = I0 + r < n && t < d ? X[(I0 + r) * ld + t] : 0.0f;
-        xj[t][r] = J0 + r < n && t < d ? X[(J0 + r) * ld + t] : 0.0f;
-    }
+    load_rows<W>(X, n, d, ld, I0, 0, [&](int r, int t, float v) { xi[r][t] = v; });
+    load_rows<W>(X, n, d, ld, J0, 0, [&](int r, int t, float v) { xj[t][r] = v; });
     __syncthreads();
-    float v[16];
+    float y[W];
+#pragma unroll
+    for (int t = 0; t < W; ++t) y[t] = xj[t][lane];
     bool big = false;
 #pragma unroll 1
     for (int r = 0; r < 16; ++r) {
-        float p[DT];
+        float p[W];
 #pragma unroll
-        for (int g = 0; g < DT; g += 8) {
-#pragma unroll
-            for (int t = g; t < g + 8; ++t) p[t] = 0.0f;
-            if (g < d) {
-#pragma unroll
-                for (int t = g; t < g + 8; ++t) {
-                    const float df = xi[16 * w + r][t] - xj[t][lane];
-                    p[t] = fmaf(df, df, 0.0f);
-                }
-            }
+        for (int t = 0; t < W; ++t) {
+            const float df = xi[16 * w + r][t] - y[t];
+            p[t] = fmaf(df, df, 0.0f);
         }
 #pragma unroll
-        for (int o = DT / 2; o >= 1; o >>= 1)
+        for (int o = W / 2; o >= 1; o >>= 1)
 #pragma unroll
             for (int t = 0; t < o; ++t) p[t] = p[t] + p[t + o];
-        // (r is not a constant: the store goes to the thread's own tile slot)
+        // (r is not a constant: the value goes to the thread's own tile slot)
         tile[16 * w + r][lane] = p[0];
         big |= too_big(p[0]);
     }
+    float v[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = tile[16 * w + r][lane];
     if (big) st->bad = 1;
-    put_tile(tile, v, n, I0, J0, D);
+    put_tile(tile, v, n, nd, I0, J0, D);
+}
+
+// Sums over the 64 lanes of 16 values, each in the order of an xor butterfly
+// (distances 32, 16, 8, 4, 2, 1): the first four steps also halve the values
+// that a lane carries on with, so that lanes 4 q .. 4 q + 3 end with value q.
+__device__ __forceinline__ float sum_scatter16(const float (&v)[16], int lane) {
+    float a[8], b[4], c[2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[q]), __float_as_uint(v[q + 8]), false, false);
+        a[q] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[q]), __float_as_uint(a[q + 4]), false, false);
+        b[q] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const bool up = lane & 8;
+        c[q] = (up ? b[q + 2] : b[q]) + __shfl_xor(up ? b[q] : b[q + 2], 8, 64);
+    }
+    const bool up = lane & 4;
+    float t = (up ? c[1] : c[0]) + __shfl_xor(up ? c[0] : c[1], 4, 64);
+    t = t + __shfl_xor(t, 2, 64);
+    return t + __shfl_xor(t, 1, 64);
 }
 
 // FP32 distances, d > 64: a wave holds 4 x 4 pairs, lane l its partial sums over
 // coordinates l, l + 64, ..., and the butterfly follows, as in the recheck.
-// Eight loads feed sixteen pairs.
+// Eight loads feed sixteen pairs.  The tree of n = 4096, d = 128: 0.81 ms with a
+// whole butterfly for each pair, 0.41 with the halving one.
 __global__ __launch_bounds__(256) void k_dense_f32(const float *__restrict__ X, int64_t n, int64_t d, int64_t ld,
-                                                   float *__restrict__ D, DenseState *__restrict__ st) {
+                                                   int64_t nd, float *__restrict__ D, DenseState *__restrict__ st) {
     constexpr int B = 4;
     if (blockIdx.y < blockIdx.x) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -141,34 +188,23 @@ __global__ __launch_bounds__(256) void k_dense_f32(const float *__restrict__ X, 
                     acc[a][b] = fmaf(df, df, acc[a][b]);
                 }
         }
+        float v[B * B];
 #pragma unroll
-        for (int a = 0; a < B; ++a)
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) acc[a][b] = acc[a][b] + __shfl_xor(acc[a][b], o, 64);
-                big |= too_big(acc[a][b]);
-            }
-        // lane 4 a + b writes pair (a, b), lane 16 + 4 b + a its mirror
-        float mine = 0.0f;
-#pragma unroll
-        for (int a = 0; a < B; ++a)
-#pragma unroll
-            for (int b = 0; b < B; ++b)
-                if (lane == B * a + b || lane == B * B + B * b + a) mine = acc[a][b];
-        if (lane < 2 * B * B) {
-            const int h = lane & (B * B - 1);
-            const bool mir = lane >= B * B;
-            const int64_t i = I0 + B * s + (mir ? h % B : h / B), j = J0 + (mir ? h / B : h % B);
-            if (i < n && j < n) D[mir ? j * n + i : i * n + j] = i == j ? inf : mine;
-        }
+        for (int q = 0; q < B * B; ++q) v[q] = acc[q / B][q % B];
+        const float mine = sum_scatter16(v, lane);
+        big |= too_big(mine);
+        // lanes 4 q .. 4 q + 3 hold pair q = (a, b): the first writes it, the second its mirror
+        const int q = lane >> 2;
+        const int64_t i = I0 + B * s + q / B, j = J0 + q % B;
+        if ((lane & 3) == 0 && i < n && j < nd) D[i * nd + j] = i == j || j >= n ? inf : mine;
+        if ((lane & 3) == 1 && i < n && j < n) D[j * nd + i] = i == j ? inf : mine;
     }
     if (big) st->bad = 1;
 }
 
 // FP64 distances: left to right over the coordinates, one thread per pair.
 __global__ __launch_bounds__(256) void k_dense_f64(const float *__restrict__ X, int64_t n, int64_t d, int64_t ld,
-                                                   double *__restrict__ D, DenseState *__restrict__ st) {
+                                                   int64_t nd, double *__restrict__ D, DenseState *__restrict__ st) {
     constexpr int C = 32;  // coordinates per chunk
     if (blockIdx.y < blockIdx.x) return;
     __shared__ double tile[DT][DT + 1];
@@ -181,11 +217,8 @@ __global__ __launch_bounds__(256) void k_dense_f64(const float *__restrict__ X, 
     for (int64_t c = 0; c < d; c += C) {
         const int m = (int)min((int64_t)C, d - c);
         __syncthreads();
-        for (int q = threadIdx.x; q < DT * C; q += 256) {
-            const int r = q / C, t = q % C;
-            xi[r][t] = I0 + r < n && t < m ? X[(I0 + r) * ld + c + t] : 0.0f;
-            xj[t][r] = J0 + r < n && t < m ? X[(J0 + r) * ld + c + t] : 0.0f;
-        }
+        load_rows<C>(X, n, d, ld, I0, c, [&](int r, int t, float x) { xi[r][t] = x; });
+        load_rows<C>(X, n, d, ld, J0, c, [&](int r, int t, float x) { xj[t][r] = x; });
         __syncthreads();
 #pragma unroll 2
         for (int t = 0; t < m; ++t) {
@@ -202,7 +235,7 @@ __global__ __launch_bounds__(256) void k_dense_f64(const float *__restrict__ X, 
 #pragma unroll
     for (int r = 0; r < 16; ++r) big |= too_big(v[r]);
     if (big) st->bad = 1;
-    put_tile(tile, v, n, I0, J0, D);
+    put_tile(tile, v, n, nd, I0, J0, D);
 }
 
 // Every point its own component; no edges yet (0, 0: valid ids for what reads
@@ -219,7 +252,7 @@ __global__ void k_dense_init(int64_t n, int32_t *__restrict__ comp, int32_t *__r
 struct RoundLDS {
     unsigned long long k1[DENSE_MAX_N];  // a component's least D^2
     uint32_t k2[DENSE_MAX_N];            // then its edge, smaller id in the high half
-    uint16_t comp[DENSE_MAX_N];
+    uint16_t comp[DENSE_MAX_N + 4];
     uint16_t par[DENSE_MAX_N];
     uint16_t id[DENSE_MAX_N];
     int32_t last, edges, ncomp, bad;
@@ -232,7 +265,7 @@ struct RoundLDS {
 // roots of the pairs that chose the same edge, pointer jumping and new labels.
 // D^2 is nonnegative, so its bits order like the values.
 template <class T>
-__global__ __launch_bounds__(DB) void k_dense_round(int64_t n, const T *__restrict__ D, int32_t *__restrict__ comp,
+__global__ __launch_bounds__(DB) void k_dense_round(int64_t n, int64_t nd, const T *__restrict__ D, int32_t *__restrict__ comp,
                                                     unsigned long long *__restrict__ rowv, int32_t *__restrict__ rowj,
                                                     int32_t *__restrict__ eu, int32_t *__restrict__ ev,
                                                     DenseState *__restrict__ st) {
@@ -242,19 +275,38 @@ __global__ __launch_bounds__(DB) void k_dense_round(int64_t n, const T *__restri
     const int tid = threadIdx.x, lane = tid & 63;
     const int nn = (int)n;
     const int i = (int)blockIdx.x * (DB / 64) + (tid >> 6);
+    constexpr int V = 16 / sizeof(T);  // values per load
+    typedef U Vec __attribute__((ext_vector_type(V)));
+    // the labels of all columns, V of them next to each other as the loads are
+    for (int q = tid; q < (int)nd; q += DB) S.comp[q] = q < nn ? (uint16_t)comp[q] : (uint16_t)0;
+    __syncthreads();
     if (i < nn) {
-        const int ci = comp[i];
-        const U *row = reinterpret_cast<const U *>(D + (int64_t)i * n);
+        const int ci = S.comp[i];
+        const Vec *row = reinterpret_cast<const Vec *>(D + (int64_t)i * nd);
+        const int nv = (int)(nd / V);
         U bv = ~U(0);
         int bj = -1;
-#pragma unroll 4
-        for (int j = lane; j < nn; j += 64) {
-            const U v = row[j];
-            if (comp[j] != ci && v < bv) {
-                bv = v;
-                bj = j;
+        // (every load of a batch is in flight before the first is looked at; the
+        // padding's +inf is the row's own label's or above every distance)
+        constexpr int AHEAD = 8;
+        for (int q0 = 0; q0 < nv; q0 += 64 * AHEAD) {
+            Vec v[AHEAD];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) v[a] = row[min(q0 + 64 * a + lane, nv - 1)];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                const int q = q0 + 64 * a + lane;
+                if (q >= nv) continue;
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    if (S.comp[q * V + e] != ci && v[a][e] < bv) {
+                        bv = v[a][e];
+                        bj = q * V + e;
+                    }
+                }
             }
         }
+        if (bj >= nn) bj = -1;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
             const U ov = (U)__shfl_xor((unsigned long long)bv, o, 64);
@@ -269,14 +321,18 @@ __global__ __launch_bounds__(DB) void k_dense_round(int64_t n, const T *__restri
             rowj[i] = bj;
         }
     }
-    __threadfence();  // this workgroup's rows before its arrival
+    // This workgroup's rows before its arrival, the others' before the reads.
+    // (One fence per workgroup, between barriers, orders all its waves; each
+    // writes back the L2: with one per wave a round of n = 2000 took 46 us, 15 so.)
     __syncthreads();
-    if (tid == 0) S.last = atomicAdd(&st->arrived, 1) == (int)gridDim.x - 1;
+    if (tid == 0) {
+        __threadfence();
+        S.last = atomicAdd(&st->arrived, 1) == (int)gridDim.x - 1;
+        __threadfence();
+    }
     __syncthreads();
     if (!S.last) return;
-    __threadfence();
     const int nc = st->ncomp;
-    for (int q = tid; q < nn; q += DB) S.comp[q] = (uint16_t)comp[q];
     for (int c = tid; c < nc; c += DB) {
         S.k1[c] = ~0ull;
         S.k2[c] = ~0u;
@@ -348,15 +404,20 @@ __global__ __launch_bounds__(DB) void k_dense_round(int64_t n, const T *__restri
         }
     }
     __syncthreads();
+    // (in place: a pointer only ever moves to an ancestor, twice as far each time)
     for (int span = 1; span < nc; span *= 2) {
-        int p[PER];
+        bool moved = false;
 #pragma unroll
-        for (int e = 0; e < PER; ++e) p[e] = tid + e * DB < nc ? S.par[S.par[tid + e * DB]] : 0;
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < PER; ++e)
-            if (tid + e * DB < nc) S.par[tid + e * DB] = (uint16_t)p[e];
-        __syncthreads();
+        for (int e = 0; e < PER; ++e) {
+            const int c = tid + e * DB;
+            if (c >= nc) continue;
+            const int p = S.par[c], g = S.par[p];
+            if (g != p) {
+                S.par[c] = (uint16_t)g;
+                moved = true;
+            }
+        }
+        if (!__syncthreads_or(moved)) break;
     }
     for (int q = tid; q < nn; q += DB) comp[q] = S.id[S.par[S.comp[q]]];
     if (tid == 0) {
@@ -466,8 +527,11 @@ __global__ __launch_bounds__(DB) void k_dense_root(int64_t n, const int32_t *__r
 
 }  // namespace
 
+// Columns of a row of the matrix: whole 16-byte loads.
+static int64_t row_stride(int64_t n) { return (n + 3) / 4 * 4; }
+
 size_t dense_bytes(int64_t n, bool f64) {
-    return align_up((size_t)(n * n) * (f64 ? 8 : 4), 256) + align_up((size_t)n * 8, 256) + align_up((size_t)n * 4, 256);
+    return align_up((size_t)(n * row_stride(n)) * (f64 ? 8 : 4), 256) + align_up((size_t)n * 8, 256) + align_up((size_t)n * 4, 256);
 }
 
 void launch_dense_tree(const DenseArgs &A, hipStream_t s) {
@@ -477,26 +541,32 @@ void launch_dense_tree(const DenseArgs &A, hipStream_t s) {
     char *p = static_cast<char *>(A.buf);
     float *const Df = reinterpret_cast<float *>(p);
     double *const Dd = reinterpret_cast<double *>(p);
-    p += align_up((size_t)(n * n) * (A.f64 ? 8 : 4), 256);
+    const int64_t nd = row_stride(n);
+    p += align_up((size_t)(n * nd) * (A.f64 ? 8 : 4), 256);
     unsigned long long *const rowv = reinterpret_cast<unsigned long long *>(p);
     p += align_up((size_t)n * 8, 256);
     int32_t *const rowj = reinterpret_cast<int32_t *>(p);
     hipLaunchKernelGGL(k_dense_init, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, A.comp, A.eu, A.ev, A.st);
     LAUNCH_CHECK();
     const unsigned t64 = (unsigned)((n + DT - 1) / DT), t16 = (unsigned)((n + 15) / 16);
-    if (A.f64)
-        hipLaunchKernelGGL(k_dense_f64, dim3(t64, t64), dim3(256), 0, s, A.X, n, A.d, A.ld, Dd, A.st);
-    else if (A.d <= 64)
-        hipLaunchKernelGGL(k_dense_f32_low, dim3(t64, t64), dim3(256), 0, s, A.X, n, A.d, A.ld, Df, A.st);
-    else
-        hipLaunchKernelGGL(k_dense_f32, dim3(t16, t16), dim3(256), 0, s, A.X, n, A.d, A.ld, Df, A.st);
+    if (A.f64) {
+        hipLaunchKernelGGL(k_dense_f64, dim3(t64, t64), dim3(256), 0, s, A.X, n, A.d, A.ld, nd, Dd, A.st);
+    } else if (A.d <= 64) {
+        auto kern = A.d <= 8    ? k_dense_f32_low<8>
+                    : A.d <= 16 ? k_dense_f32_low<16>
+                    : A.d <= 32 ? k_dense_f32_low<32>
+                                : k_dense_f32_low<64>;
+        hipLaunchKernelGGL(kern, dim3(t64, t64), dim3(256), 0, s, A.X, n, A.d, A.ld, nd, Df, A.st);
+    } else {
+        hipLaunchKernelGGL(k_dense_f32, dim3(t16, t16), dim3(256), 0, s, A.X, n, A.d, A.ld, nd, Df, A.st);
+    }
     LAUNCH_CHECK();
     const dim3 g((unsigned)((n + DB / 64 - 1) / (DB / 64)));
     for (int64_t c = 1; c < n; c *= 2) {  // a round at least halves the components
         if (A.f64)
-            hipLaunchKernelGGL(k_dense_round<double>, g, dim3(DB), 0, s, n, Dd, A.comp, rowv, rowj, A.eu, A.ev, A.st);
+            hipLaunchKernelGGL(k_dense_round<double>, g, dim3(DB), 0, s, n, nd, Dd, A.comp, rowv, rowj, A.eu, A.ev, A.st);
         else
-            hipLaunchKernelGGL(k_dense_round<float>, g, dim3(DB), 0, s, n, Df, A.comp, rowv, rowj, A.eu, A.ev, A.st);
+            hipLaunchKernelGGL(k_dense_round<float>, g, dim3(DB), 0, s, n, nd, Df, A.comp, rowv, rowj, A.eu, A.ev, A.st);
         LAUNCH_CHECK();
     }
 }

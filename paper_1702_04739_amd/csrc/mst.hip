@@ -3436,9 +3436,9 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
 // points (16-bit ids, the join's and the rooting's tables in LDS) and
 // DENSE_MAX_WORK coordinate differences, and only where the call leaves
 // everything to the library: a screen precision other than FP32 and any flag
-// ask for the screened rounds.  Both sides, FP32 recheck, us: n = 150, d = 5: 142
-// and 746; n = 2048, d = 16: 270 and 1128; n = 4096, d = 16 / 784 / 4096: 563 and
-// 1299 / 1396 and 2112 / 4526 and 6888 (FP64 recheck 8611 and 8679, where the work
+// ask for the screened rounds.  Both sides, FP32 recheck, us: n = 150, d = 5: 111
+// and 644; n = 2000, d = 16: 159 and 997; n = 4096, d = 16 / 784 / 4096: 238 and
+// 1254 / 996 and 2106 / 4287 and 6641 (FP64 recheck 7511 and 8435: there the work
 // limit lies).
 constexpr double DENSE_MAX_WORK = 0x1p36;
 

@@ -349,12 +349,16 @@ __global__ __launch_bounds__(256) void k_sel_round(const double *vals, const int
     __syncthreads();
     for (int b = threadIdx.x; b < SEL_BINS; b += 256)
         if (cnt[b]) atomicAdd(&st->hist[b], cnt[b]);
-    __threadfence();  // this workgroup's counts before its arrival
+    // this workgroup's counts before its arrival, the others' before the reads:
+    // one fence per workgroup, between barriers (each writes back the L2)
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&st->finished, 1) == (int)gridDim.x - 1;
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_last = atomicAdd(&st->finished, 1) == (int)gridDim.x - 1;
+        __threadfence();
+    }
     __syncthreads();
     if (!s_last) return;
-    __threadfence();
     for (int b = threadIdx.x; b < SEL_BINS; b += 256) {
         cnt[b] = __hip_atomic_load(&st->hist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         st->hist[b] = 0;

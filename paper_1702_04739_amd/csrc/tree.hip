@@ -1350,7 +1350,8 @@ __global__ __launch_bounds__(UPPER_THREADS) void k_walk_top(WalkArgs A, int tier
                                                             int32_t *cnt_next, unsigned long long *thr_next) {
     __shared__ UpperLds L;
     if (!A.st->bad && !A.S[0].final) walk_upper(A, tier, 0, 0, 1, L);
-    __threadfence();  // the waves' atomics before the reads below
+    __syncthreads();
+    if (threadIdx.x == 0) __threadfence();  // the waves' atomics before the reads below
     __syncthreads();
     if (threadIdx.x < 64) search_step(S, A.st, Nvals, A.cnt, A.thr, cnt_next, thr_next, A.ncut, false);
 }
