@@ -167,7 +167,8 @@ void histogram_i32(const int32_t *key, int64_t n, int64_t nbins, int32_t *count,
 // Exclusive scan of int32 in[0..n) into out[0..n) (in-place allowed); writes
 // the total to *total (device) when total != nullptr.  With scratch (device,
 // scan_scratch_bytes(n)) long inputs are scanned by many workgroups; without
-// it, by one.
+// it, by one.  `in` is 16-byte aligned and readable to the end of its last
+// 16-byte group (as every array of a workspace is).
 size_t scan_scratch_bytes(int64_t n);
 void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, int32_t *total, int32_t *scratch,
                         hipStream_t s);
