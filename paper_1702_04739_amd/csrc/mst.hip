@@ -101,7 +101,8 @@ __device__ __forceinline__ int grid_exponent(float x) {
 }
 
 // Partial per-coordinate sums (FP64) and maxima of |x| over row blocks;
-// non-finite check.
+// non-finite check.  Bound by the read of X: two batches of sixteen rows in
+// flight, n = 200,000, d = 784 358 -> 225 us against eight loads at a time.
 __global__ __launch_bounds__(256) void k_colstats_partial(const float *__restrict__ X, int64_t n, int64_t d,
                                                           int64_t ld, double *__restrict__ psum,
                                                           int32_t *__restrict__ pgrid, float *__restrict__ pmin,
@@ -114,15 +115,32 @@ __global__ __launch_bounds__(256) void k_colstats_partial(const float *__restric
     int q = GRID_NONE;
     bool bad = false;
     float mn = __builtin_huge_valf(), mx = -__builtin_huge_valf();
-#pragma unroll 8
-    for (int64_t i = lo; i < hi; ++i) {
-        const float x = X[i * ld + t];
+    auto take = [&](float x) {
         bad |= !isfinite(x);
         s = s + (double)x;
         q = min(q, grid_exponent(x));
         mn = fminf(mn, x);
         mx = fmaxf(mx, x);
+    };
+    constexpr int AHEAD = 16;  // loads in flight while the ones before are taken
+    int64_t i = lo;
+    if (hi - lo >= 2 * AHEAD) {
+        float a[AHEAD], b[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) a[u] = X[(i + u) * ld + t];
+        for (; i + 2 * AHEAD <= hi; i += AHEAD) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) b[u] = X[(i + AHEAD + u) * ld + t];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) take(a[u]);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) a[u] = b[u];
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) take(a[u]);
+        i += AHEAD;
     }
+    for (; i < hi; ++i) take(X[i * ld + t]);
     psum[rb * d + t] = s;
     pgrid[rb * d + t] = q;
     pmin[rb * d + t] = mn;
@@ -248,12 +266,26 @@ __global__ __launch_bounds__(256) void k_repr_rows(const float *__restrict__ X, 
     double m2 = 0.0, e2 = 0.0;
     int q = GRID_NONE;
     int32_t si = 0;  // INT8: exact squared norm in grid units
-    for (int64_t t = lane; t < d_pad; t += 64) {
-        float xv = 0.0f, y = 0.0f;
-        if (i < n && t < d) {
-            xv = X[i * ld + t];
-            y = xv - mu[t];
+    // eight strides of the row are in flight at once (no branch between the
+    // loads), then folded in the order of one at a time: n = 200,000, d = 784
+    // 634 -> 320 us
+    constexpr int AHEAD = 8;
+    const float *const row = X + min(i, n - 1) * ld;
+    for (int64_t tb = lane; tb < d_pad; tb += 64 * AHEAD) {
+        float xs[AHEAD], ms[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int64_t tc = min(tb + 64 * u, d - 1);
+            xs[u] = row[tc];
+            ms[u] = mu[tc];
         }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+        const int64_t t = tb + 64 * u;
+        if (t >= d_pad) break;
+        const bool real = i < n && t < d;
+        const float xv = real ? xs[u] : 0.0f, mt = ms[u];
+        const float y = real ? xv - mt : 0.0f;
         float yr;
         if (REP == ISO_PREC_BF16) {
             const uint16_t b = bf16_rne(y);
@@ -279,8 +311,9 @@ __global__ __launch_bounds__(256) void k_repr_rows(const float *__restrict__ X, 
         const double yd = (double)yr;
         m2 = m2 + yd * yd;
         if (i < n && t < d) {
-            const double df = yd - ((double)xv - (double)mu[t]);
+            const double df = yd - ((double)xv - (double)mt);
             e2 = e2 + df * df;
+        }
         }
     }
 #pragma unroll
@@ -1151,52 +1184,90 @@ __global__ __launch_bounds__(1024) void k_sum_squares(const int32_t *__restrict_
 
 // ------------------------------------------------------------------ FP64 lengths and rooting
 
-// Length of each tree edge: sqrt of the FP64 left-to-right sum of squared
-// coordinate differences.
 // FP64 edge lengths: one lane per edge sums its squared coordinate differences
 // left to right (as d2_f64_lane); the two rows of the wave's 64 edges are
-// staged through LDS 16 coordinates at a time with coalesced loads.
-constexpr int REF_T = 16;
+// staged through the wave's own LDS, REF_T coordinates (a cache line of each
+// row) at a time, and the next chunk's loads are in flight while one is summed.
+// Bound by those scattered lines (2 (n - 1) rows): n = 200,000, d = 784 706 -> 266 us,
+// n = 100,000, d = 4096 1989 -> 521 us against 64-byte chunks loaded one value
+// at a time.  VEC: rows are whole aligned 16-byte groups.
+constexpr int REF_T = 32;
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_refine(const float *__restrict__ X, int64_t d, int64_t ld,
                                                 const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
                                                 int64_t m, double *__restrict__ elen) {
+    constexpr int PARTS = REF_T / 4;                // groups of four coordinates
+    constexpr int SLOTS = 2 * 64 * PARTS / 64;      // groups per lane and chunk
     __shared__ float st[4][2][64][REF_T + 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t e0 = ((int64_t)blockIdx.x * 4 + w) * 64;
-    // loader roles: slot k of this lane stages 4 coordinates of row (r) of edge
-    // e0 + ed, ed = idx / 8, r = (idx / 4) mod 2, part = idx mod 4, idx = lane + 64 k
-    const float *src[8];
+    if (e0 >= m) return;
+    // loader roles: slot k of this lane stages group `part` of row r of edge
+    // e0 + ed, idx = lane + 64 k = (ed 2 + r) PARTS + part (edges past m repeat the last)
+    const int part = lane % PARTS;
+    int64_t row[SLOTS];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int idx = lane + 64 * k;
-        const int64_t ee = e0 + (idx >> 3);
-        const int r = (idx >> 2) & 1;
-        src[k] = ee < m ? X + (int64_t)(r ? ev[ee] : eu[ee]) * ld + 4 * (idx & 3) : nullptr;
+    for (int k = 0; k < SLOTS; ++k) {
+        const int q = (lane + 64 * k) / PARTS;
+        const int64_t ee = min(e0 + (q >> 1), m - 1);
+        row[k] = (int64_t)(q & 1 ? ev[ee] : eu[ee]) * ld;
     }
+    float4 v[SLOTS];
+    auto load = [&](int64_t t0) {
+#pragma unroll
+        for (int k = 0; k < SLOTS; ++k) {
+            const int64_t t = t0 + 4 * part;
+            if constexpr (VEC) {
+                v[k] = *reinterpret_cast<const float4 *>(X + row[k] + min(t, d - 4));
+            } else {
+                const float *x = X + row[k];
+                v[k] = make_float4(x[min(t, d - 1)], x[min(t + 1, d - 1)], x[min(t + 2, d - 1)], x[min(t + 3, d - 1)]);
+            }
+        }
+    };
     double s = 0.0;
+    load(0);
     for (int64_t t0 = 0; t0 < d; t0 += REF_T) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int idx = lane + 64 * k;
-            float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (src[k]) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (t0 + 4 * (idx & 3) + c < d) v[c] = src[k][t0 + c];
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) st[w][(idx >> 2) & 1][idx >> 3][4 * (idx & 3) + c] = v[c];
+        for (int k = 0; k < SLOTS; ++k) {
+            const int q = (lane + 64 * k) / PARTS;
+            float *o = &st[w][q & 1][q >> 1][4 * part];
+            o[0] = v[k].x;
+            o[1] = v[k].y;
+            o[2] = v[k].z;
+            o[3] = v[k].w;
         }
-        __syncthreads();
+        load(t0 + REF_T);  // (past the end: the last group again, not used)
+        // a wave's LDS operations complete in order: only the compiler has to keep them so
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const int tn = d - t0 < REF_T ? (int)(d - t0) : REF_T;
-        for (int c = 0; c < tn; ++c) {
-            const double df = (double)st[w][0][lane][c] - (double)st[w][1][lane][c];
-            const double p = df * df;
-            s = s + p;
+        if (tn == REF_T) {
+#pragma unroll 8
+            for (int c = 0; c < REF_T; ++c) {
+                const double df = (double)st[w][0][lane][c] - (double)st[w][1][lane][c];
+                const double p = df * df;
+                s = s + p;
+            }
+        } else {
+            for (int c = 0; c < tn; ++c) {
+                const double df = (double)st[w][0][lane][c] - (double)st[w][1][lane][c];
+                const double p = df * df;
+                s = s + p;
+            }
         }
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     if (e0 + lane < m) elen[e0 + lane] = sqrt(s);
+}
+
+void launch_refine(const float *X, int64_t d, int64_t ld, const int32_t *eu, const int32_t *ev, int64_t m,
+                   double *elen, hipStream_t s) {
+    const bool vec = d % 4 == 0 && ld % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    hipLaunchKernelGGL(vec ? k_refine<true> : k_refine<false>, dim3(grid_for(m, 256)), dim3(256), 0, s, X, d, ld, eu,
+                       ev, m, elen);
+    LAUNCH_CHECK();
 }
 
 __global__ void k_degree(const int32_t *__restrict__ eu, const int32_t *__restrict__ ev, int64_t m,
@@ -1229,12 +1300,12 @@ __global__ void k_fill_adj(const int32_t *__restrict__ eu, const int32_t *__rest
 // after arc u -> v it takes the arc that follows v -> u in v's list
 // (cyclically); the arc that would lead back to the root's first arc (arc 0)
 // ends it.  Each arc's distance to the end of the tour comes from pointer
-// jumping (log2 of the arc count rounds); of an edge's two arcs the one taken
+// jumping; of an edge's two arcs the one taken
 // first, the farther from the end, goes from parent to child.  Whatever order
 // the adjacency lists have, the parents are the tree's unique ones.
 __global__ void k_tour_succ(const int32_t *__restrict__ off, const int32_t *__restrict__ adj,
                             const int32_t *__restrict__ adje, const int32_t *__restrict__ earc, int64_t narcs,
-                            int32_t *__restrict__ nxt, int32_t *__restrict__ rk) {
+                            int2 *__restrict__ tour) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= narcs) return;
     const int32_t e = adje[x];
@@ -1242,25 +1313,31 @@ __global__ void k_tour_succ(const int32_t *__restrict__ off, const int32_t *__re
     const int32_t v = adj[x];
     int32_t nx = r + 1 < off[v + 1] ? r + 1 : off[v];
     if (nx == 0) nx = -1;  // back at the root's first arc: the tour ends
-    nxt[x] = nx;
-    rk[x] = 1;
+    tour[x] = make_int2(nx, 1);
 }
 
-__global__ void k_tour_jump(const int32_t *__restrict__ nxt_in, const int32_t *__restrict__ rk_in, int64_t narcs,
-                            int32_t *__restrict__ nxt_out, int32_t *__restrict__ rk_out) {
+// One round: TOUR_HOPS hops along the pointers as they were, so that a pointer
+// spans TOUR_HOPS + 1 times as many arcs.  Successor and distance lie together:
+// a hop is one scattered line.  n = 200,000: 19 rounds of one hop over two
+// arrays, 22 us each; 10 rounds of 10 us so.
+constexpr int TOUR_HOPS = 3;
+
+__global__ void k_tour_jump(const int2 *__restrict__ in, int64_t narcs, int2 *__restrict__ out) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= narcs) return;
-    int32_t nx = nxt_in[x], r = rk_in[x];
-    if (nx >= 0) {
-        r += rk_in[nx];
-        nx = nxt_in[nx];
+    int2 t = in[x];
+#pragma unroll
+    for (int h = 0; h < TOUR_HOPS; ++h) {
+        if (t.x >= 0) {
+            const int2 o = in[t.x];
+            t = make_int2(o.x, t.y + o.y);
+        }
     }
-    nxt_out[x] = nx;
-    rk_out[x] = r;
+    out[x] = t;
 }
 
 __global__ void k_tour_orient(const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
-                              const int32_t *__restrict__ earc, const int32_t *__restrict__ rk,
+                              const int32_t *__restrict__ earc, const int2 *__restrict__ tour,
                               const double *__restrict__ elen, int64_t m, int32_t *__restrict__ parent,
                               double *__restrict__ length) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1270,7 +1347,7 @@ __global__ void k_tour_orient(const int32_t *__restrict__ eu, const int32_t *__r
     }
     if (e >= m) return;
     const int32_t a = eu[e], b = ev[e];
-    const bool a_first = rk[earc[2 * e]] > rk[earc[2 * e + 1]];  // arc a -> b taken before b -> a
+    const bool a_first = tour[earc[2 * e]].y > tour[earc[2 * e + 1]].y;  // arc a -> b taken before b -> a
     const int32_t child = a_first ? b : a;
     parent[child] = a_first ? a : b;
     length[child] = elen[e];
@@ -1518,15 +1595,22 @@ constexpr int PRUNE_MIN_TILES = 32;  // fewer tiles (n < 8,192): every pair is s
 constexpr int64_t PRUNE_MAX_D = 8192;  // the tile centroid is held in LDS
 constexpr int64_t PRUNE_MAX_TILES = 8192;  // the final round's supports: ntF^2 floats
 
-// Nearest pivot of each of `count` rows (row rows[r], or r when rows is null),
-// by FP32 sums of squared differences; 128 rows x PIV pivots per workgroup
+// Squared distances of the pivots from each other, one wave per pair (the order
+// of the pivots depends on them, no result does).
+__global__ __launch_bounds__(256) void k_pivot_dist(const float *__restrict__ X, int64_t d, int64_t ld,
+                                                    const int32_t *__restrict__ piv, float *__restrict__ dist) {
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q >= PIV * PIV) return;
+    const float v = d2_f32_wave(X + (int64_t)piv[q / PIV] * ld, X + (int64_t)piv[q % PIV] * ld, d);
+    if ((threadIdx.x & 63) == 0) dist[q] = v;
+}
+
+// Nearest pivot of every row, by FP32 sums of squared differences; 128 rows x PIV pivots per workgroup
 // (thread t: rows 4 (t / 8) .. +3, pivots 4 (t mod 8) .. +3), 64 coordinates
-// at a time through LDS; ties go to the smaller pivot index.  dist (nullable)
-// receives the PIV squared distances of every row.
+// at a time through LDS; ties go to the smaller pivot index.
 __global__ __launch_bounds__(256) void k_pivot_near(const float *__restrict__ X, int64_t d, int64_t ld,
-                                                    const int32_t *__restrict__ rows, int64_t count,
-                                                    const int32_t *__restrict__ piv, uint32_t *__restrict__ key,
-                                                    float *__restrict__ dist) {
+                                                    int64_t count,
+                                                    const int32_t *__restrict__ piv, uint32_t *__restrict__ key) {
     static_assert(PIV == 32, "eight groups of four pivots");
     __shared__ float sx[128][65];
     __shared__ float sp[PIV][65];
@@ -1535,7 +1619,7 @@ __global__ __launch_bounds__(256) void k_pivot_near(const float *__restrict__ X,
     const int64_t r0 = (int64_t)blockIdx.x * 128;
     if (tid < 128) {
         const int64_t g = r0 + tid;
-        roff[tid] = g < count ? (rows ? (int64_t)rows[g] : g) * ld : -1;
+        roff[tid] = g < count ? g * ld : -1;
     } else if (tid < 128 + PIV) {
         roff[tid] = (int64_t)piv[tid - 128] * ld;
     }
@@ -1604,9 +1688,6 @@ __global__ __launch_bounds__(256) void k_pivot_near(const float *__restrict__ X,
         }
         if (g < count) {
             if (tp == 0) key[g] = (uint32_t)bi;
-            if (dist)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) dist[g * PIV + 4 * tp + b] = acc[a][b];
         }
     }
 }
@@ -2126,7 +2207,8 @@ struct MstPlan {
     double *psum;
     uint32_t *rmax, *emax, *comp_ub;
     int32_t *comp, *ccnt, *cj, *glist, *gcnt, *gcj, *rlist, *rb_j, *cpar, *npar, *flag, *newid, *eu, *ev;
-    int32_t *deg, *aoff, *cursor, *adj, *adje, *earc, *tnxt0, *tnxt1, *trk0, *trk1;
+    int32_t *deg, *aoff, *cursor, *adj, *adje, *earc;
+    int2 *tour0, *tour1;
     float *ltau, *lv;               // neighbour lists: thresholds, [n][LIST_CAP] values
     int32_t *lscnt, *lj;            // entries offered, [n][LIST_CAP] partners
     uint32_t *ldrop;                // smallest dropped value
@@ -2199,10 +2281,8 @@ struct MstPlan {
         adj = a.take<int32_t>(2 * n);
         adje = a.take<int32_t>(2 * n);
         earc = a.take<int32_t>(2 * n);   // the two arcs of each tree edge
-        tnxt0 = a.take<int32_t>(2 * n);  // Euler tour: successor and distance to the end, double-buffered
-        tnxt1 = a.take<int32_t>(2 * n);
-        trk0 = a.take<int32_t>(2 * n);
-        trk1 = a.take<int32_t>(2 * n);
+        tour0 = a.take<int2>(2 * n);     // Euler tour: successor and distance to the end, double-buffered
+        tour1 = a.take<int2>(2 * n);
         rb_d2 = a.take<double>(n);
         elen = a.take<double>(n);
         wsum = a.take<double>(1);
@@ -2473,7 +2553,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
         HIP_CHECK(hipMemcpyAsync(P.piv, h_piv.data(), sizeof(int32_t) * PIV, hipMemcpyHostToDevice, s));
         aux.after(s);
         hipLaunchKernelGGL(k_pivot_near, dim3((unsigned)((n + 127) / 128)), dim3(256), 0, aux.s, X, d, ld,
-                           static_cast<const int32_t *>(nullptr), n, P.piv, P.pkeys, static_cast<float *>(nullptr));
+                           n, P.piv, P.pkeys);
         LAUNCH_CHECK();
         HIP_CHECK(hipEventRecord(aux.ev_key, aux.s));
     }
@@ -2622,10 +2702,8 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     if (prune) {
         // The first round's order: the points by their nearest pivot, the
         // pivots in a nearest-neighbour chain from the first; component labels
-        // follow the order.  (The pivots' own distances: keys into the sort's
-        // spare keys, which the assignment on the second stream does not touch.)
-        hipLaunchKernelGGL(k_pivot_near, dim3(1), dim3(256), 0, s, X, d, ld, P.piv, (int64_t)PIV, P.piv, P.ptk,
-                           P.pivd);
+        // follow the order.
+        hipLaunchKernelGGL(k_pivot_dist, dim3(PIV * PIV / 4), dim3(256), 0, s, X, d, ld, P.piv, P.pivd);
         LAUNCH_CHECK();
         std::vector<float> pd((size_t)PIV * PIV);
         R.get(pd.data(), P.pivd, sizeof(float) * pd.size(), s);
@@ -3372,9 +3450,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     // them only for its last step: with the second stream started they run
     // there, beside the rooting's small latency-bound launches.
     if (aux.s) aux.after(s);
-    hipLaunchKernelGGL(k_refine, dim3(grid_for(m, 256)), dim3(256), 0, aux.s ? aux.s : s, X, d, ld, P.eu, P.ev, m,
-                       P.elen);
-    LAUNCH_CHECK();
+    launch_refine(X, d, ld, P.eu, P.ev, m, P.elen, aux.s ? aux.s : s);
     if (aux.s) HIP_CHECK(hipEventRecord(aux.ev_len, aux.s));
     fill<int32_t>(P.deg, 0, n + 1, s);
     hipLaunchKernelGGL(k_degree, dim3(grid_for(m, 256)), dim3(256), 0, s, P.eu, P.ev, m, P.deg);
@@ -3387,13 +3463,12 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     // rooting: Euler tour, pointer jumping, orientation
     const int64_t narcs = 2 * m;
     hipLaunchKernelGGL(k_tour_succ, dim3(grid_for(narcs, 256)), dim3(256), 0, s, P.aoff, P.adj, P.adje, P.earc, narcs,
-                       P.tnxt0, P.trk0);
+                       P.tour0);
     LAUNCH_CHECK();
-    int32_t *tn = P.tnxt0, *tr = P.trk0, *tn2 = P.tnxt1, *tr2 = P.trk1;
-    for (int64_t span = 1; span < narcs; span *= 2) {
-        hipLaunchKernelGGL(k_tour_jump, dim3(grid_for(narcs, 256)), dim3(256), 0, s, tn, tr, narcs, tn2, tr2);
+    int2 *tr = P.tour0, *tr2 = P.tour1;
+    for (int64_t span = 1; span < narcs; span *= TOUR_HOPS + 1) {
+        hipLaunchKernelGGL(k_tour_jump, dim3(grid_for(narcs, 256)), dim3(256), 0, s, tr, narcs, tr2);
         LAUNCH_CHECK();
-        std::swap(tn, tn2);
         std::swap(tr, tr2);
     }
     if (aux.s) HIP_CHECK(hipStreamWaitEvent(s, aux.ev_len, 0));  // the lengths
@@ -3402,7 +3477,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     LAUNCH_CHECK();
     // the tour from the root covers every arc exactly when the edges form one tree
     int32_t h_tour[2] = {0, 0};
-    R.get(&h_tour[0], tr, sizeof(int32_t), s);
+    R.get(&h_tour[0], &tr[0].y, sizeof(int32_t), s);
     R.get(&h_tour[1], P.aoff + 1, sizeof(int32_t), s);
     hipLaunchKernelGGL(k_sum_lengths, dim3(1), dim3(1024), 0, s, length, n, P.wsum);
     LAUNCH_CHECK();
@@ -3487,8 +3562,7 @@ bool dense_mst(const float *X, int64_t n, int64_t d, int64_t ld, bool f64, int32
     const int64_t m = n - 1;
     double *const wsum = reinterpret_cast<double *>(P.out + DensePlan::OUT_BYTES - sizeof(double));
     launch_dense_tree(P.A, s);
-    hipLaunchKernelGGL(k_refine, dim3(grid_for(m, 256)), dim3(256), 0, s, X, d, ld, P.A.eu, P.A.ev, m, P.elen);
-    LAUNCH_CHECK();
+    launch_refine(X, d, ld, P.A.eu, P.A.ev, m, P.elen, s);
     launch_dense_root(P.A, P.elen, parent, length, s);
     hipLaunchKernelGGL(k_sum_lengths, dim3(1), dim3(1024), 0, s, length, n, wsum);
     LAUNCH_CHECK();
