@@ -257,7 +257,16 @@ __global__ __launch_bounds__(256) void k_repr_rows(const float *__restrict__ X, 
                                                    float inv_step) {
     const int lane = threadIdx.x & 63;
     // rows are walked with the stride of all waves; the maxima of r and e and
-    // the grid exponent are merged into the globals once per wave
+    // the grid exponent are merged in LDS and into the globals once per
+    // workgroup (once per wave, 8,192 waves queue at three addresses: 107 us at
+    // n = 50,000, d = 64, 32 so)
+    __shared__ uint32_t gr, ge;
+    __shared__ int gq;
+    if (threadIdx.x == 0) {
+        gr = ge = 0u;
+        gq = GRID_NONE;
+    }
+    __syncthreads();
     uint32_t wr = 0u, we = 0u;
     int wq = GRID_NONE;
     const int64_t nwaves = (int64_t)gridDim.x * 4;
@@ -337,9 +346,16 @@ __global__ __launch_bounds__(256) void k_repr_rows(const float *__restrict__ X, 
     we = max(we, __float_as_uint(e));
     }
     if (lane == 0) {
-        if (wq != GRID_NONE) atomicMin(grid_min, wq);
-        if (wr) atomicMax(rmax_bits, wr);
-        if (we) atomicMax(emax_bits, we);
+        if (wq != GRID_NONE) atomicMin(&gq, wq);
+        if (wr) atomicMax(&gr, wr);
+        if (we) atomicMax(&ge, we);
+    }
+    __syncthreads();
+    // (a value read early can only be further from the final one)
+    if (threadIdx.x == 0) {
+        if (gq < *(const volatile int32_t *)grid_min) atomicMin(grid_min, gq);
+        if (gr > *(const volatile uint32_t *)rmax_bits) atomicMax(rmax_bits, gr);
+        if (ge > *(const volatile uint32_t *)emax_bits) atomicMax(emax_bits, ge);
     }
 }
 
@@ -518,8 +534,15 @@ __device__ inline bool row_threshold(const float *__restrict__ best, const float
     return true;
 }
 
-// One wave per row: exact recheck of the sweep's candidates.  Rows whose
+// Exact recheck of the sweep's candidates, RCK_ROWS rows per wave.  Rows whose
 // list overflowed, and rows marked SCR_FORCE, are queued for the gathered pass.
+// A row has one or two candidates to evaluate, and a wave per row is a chain of
+// five dependent loads for each; so lane r holds row r's counts and thresholds, the
+// candidates that pass are packed into LDS, and the packed pairs are evaluated
+// four at a time (FP64 order: one per lane).  n = 200,000, d = 784: 195 -> 86 us a
+// round, n = 50,000, d = 64: 95 -> 16.
+constexpr int RCK_ROWS = 16;
+
 template <bool F64>
 __global__ __launch_bounds__(256) void k_recheck_rows(const float *__restrict__ X, int64_t n, int64_t d, int64_t ld,
                                                       const float *__restrict__ best, const float *__restrict__ Emax,
@@ -529,32 +552,118 @@ __global__ __launch_bounds__(256) void k_recheck_rows(const float *__restrict__ 
                                                       const float *__restrict__ cl, float kappa, float dn,
                                                       double *__restrict__ rb_d2, int32_t *__restrict__ rb_j,
                                                       int32_t *__restrict__ glist, int32_t *__restrict__ counters) {
-    const int lane = threadIdx.x & 63;
-    int evaluated = 0;
-    // rows are walked with the stride of all waves (a few thousand workgroups
-    // instead of one per four rows: the dispatch of 50k small workgroups costs
-    // more than their work)
-    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
-        double out_d2 = __builtin_huge_val();
-        int out_j = -1, ev = 0;
-        float thr;
-        const int cnt = ccnt[i];
-        if (cnt == SCR_FORCE) {
-            if (lane == 0) glist[atomicAdd(&counters[C_GATHER], 1)] = (int32_t)i;
-        } else if (row_threshold(best, Emax, ub, comp, comp_ub, i, kappa, dn, thr)) {
-            if (cnt > SCR_CAP) {
-                if (lane == 0) glist[atomicAdd(&counters[C_GATHER], 1)] = (int32_t)i;
-            } else {
-                eval_candidates<F64>(X, ld, d, i, cj + i * SCR_CAP, cl + i * SCR_CAP, cnt, thr, out_d2, out_j, ev);
+    static_assert(RCK_ROWS * SCR_CAP % 64 == 0 && 64 % SCR_CAP == 0 && RCK_ROWS <= 64, "lists by whole waves");
+    __shared__ int32_t pj[4][RCK_ROWS * SCR_CAP];
+    __shared__ uint8_t pr[4][RCK_ROWS * SCR_CAP];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __shared__ int32_t evaluated;
+    if (threadIdx.x == 0) evaluated = 0;
+    __syncthreads();
+    const int64_t base = ((int64_t)blockIdx.x * 4 + w) * RCK_ROWS;  // (a wave past the rows holds none)
+    const int64_t mine = base + (lane & (RCK_ROWS - 1)), i = min(mine, n - 1);
+    const bool holder = lane < RCK_ROWS && mine < n;
+    const int cnt = ccnt[i];
+    float thr = 0.0f;
+    const bool open = row_threshold(best, Emax, ub, comp, comp_ub, i, kappa, dn, thr);
+    const bool gather = cnt == SCR_FORCE || (open && cnt > SCR_CAP);
+    if (holder && gather) glist[atomicAdd(&counters[C_GATHER], 1)] = (int32_t)i;
+    const int have = open && !gather && mine < n ? cnt : 0;
+    // the candidates within their row's threshold, row by row
+    constexpr int STEPS = RCK_ROWS * SCR_CAP / 64;
+    float l[STEPS];
+    int32_t jc[STEPS];
+    int hv[STEPS];
+    const int q = lane & (SCR_CAP - 1);
+#pragma unroll
+    for (int e = 0; e < STEPS; ++e) {
+        const int r = (e * 64 + lane) / SCR_CAP;
+        hv[e] = __shfl(have, r, 64);
+        // (a slot past the count reads the row's first one)
+        const int64_t at = min(base + r, n - 1) * SCR_CAP + (q < hv[e] ? q : 0);
+        l[e] = cl[at];
+        jc[e] = cj[at];
+    }
+    int total = 0;
+#pragma unroll
+    for (int e = 0; e < STEPS; ++e) {
+        const int r = (e * 64 + lane) / SCR_CAP;
+        const float t = __shfl(thr, r, 64);  // (by every lane: not under the condition)
+        const bool pass = q < hv[e] && l[e] <= t;
+        const unsigned long long bal = __ballot(pass);
+        if (pass) {
+            const int at = total + __popcll(bal & ((1ull << lane) - 1ull));
+            pj[w][at] = jc[e];
+            pr[w][at] = (uint8_t)r;
+        }
+        total += __popcll(bal);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    double out_d2 = __builtin_huge_val();  // lane r: row r's lightest
+    int out_j = -1;
+    if constexpr (!F64) {
+        constexpr int G = 4;
+#pragma unroll 1
+        for (int g = 0; g < total; g += G) {
+            const float *x[G], *y[G];
+            int rr[G], jj[G];
+#pragma unroll
+            for (int a = 0; a < G; ++a) {
+                const int at = min(g + a, total - 1);
+                rr[a] = __builtin_amdgcn_readfirstlane((int)pr[w][at]);
+                jj[a] = __builtin_amdgcn_readfirstlane(pj[w][at]);
+                x[a] = X + (base + rr[a]) * ld;
+                y[a] = X + (int64_t)jj[a] * ld;
+            }
+            // (each pair in the order of d2_f32_wave)
+            float acc[G] = {};
+#pragma unroll 4
+            for (int64_t t = lane; t < d; t += 64) {
+#pragma unroll
+                for (int a = 0; a < G; ++a) {
+                    const float df = x[a][t] - y[a][t];
+                    acc[a] = fmaf(df, df, acc[a]);
+                }
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+                for (int a = 0; a < G; ++a) acc[a] += __shfl_xor(acc[a], off, 64);
+#pragma unroll
+            for (int a = 0; a < G; ++a) {
+                const double d2 = (double)acc[a];
+                if (lane == rr[a] && key_less(d2, jj[a], out_d2, out_j)) {
+                    out_d2 = d2;
+                    out_j = jj[a];
+                }
             }
         }
-        if (lane == 0) {
-            rb_d2[i] = out_d2;
-            rb_j[i] = out_j;
+    } else {
+#pragma unroll 1
+        for (int g = 0; g < total; g += 64) {
+            const int at = min(g + lane, total - 1);
+            const int r = pr[w][at], j = pj[w][at];
+            const double d2 = g + lane < total ? d2_f64_lane(X + (base + r) * ld, X + (int64_t)j * ld, d) : 0.0;
+            const int m = min(64, total - g);
+#pragma unroll 1
+            for (int p = 0; p < m; ++p) {
+                const double pd = __shfl(d2, p, 64);
+                const int prow = __shfl(r, p, 64), pjj = __shfl(j, p, 64);
+                if (lane == prow && key_less(pd, pjj, out_d2, out_j)) {
+                    out_d2 = pd;
+                    out_j = pjj;
+                }
+            }
         }
-        evaluated += ev;
     }
-    if (lane == 0 && evaluated) atomicAdd((unsigned long long *)&counters[C_CAND], (unsigned long long)evaluated);
+    if (holder) {
+        rb_d2[mine] = out_d2;
+        rb_j[mine] = out_j;
+    }
+    if (lane == 0 && total) atomicAdd(&evaluated, total);
+    __syncthreads();
+    if (threadIdx.x == 0 && evaluated)
+        atomicAdd((unsigned long long *)&counters[C_CAND], (unsigned long long)evaluated);
 }
 
 // One wave per gathered row: exact recheck of the gathered pass's candidates;
@@ -1409,7 +1518,7 @@ __global__ void k_tile_ranges(const int32_t *__restrict__ perm, const int32_t *_
 // pairs of the kept ones (C_PAIRS: cnt_I cnt_J off the diagonal; on it
 // cnt (cnt - 1) / 2 when diag_all, i.e. every point its own component, else 0,
 // since a diagonal tile's pairs within one component are not counted).
-__global__ void k_pair_keep(const int2 *__restrict__ pairs, int64_t npairs, const int32_t *__restrict__ tlo,
+__global__ __launch_bounds__(256) void k_pair_keep(const int2 *__restrict__ pairs, int64_t npairs, const int32_t *__restrict__ tlo,
                             const int32_t *__restrict__ thi, const float *__restrict__ plb,
                             const float *__restrict__ tthr, const int32_t *__restrict__ tcnt, int phase,
                             int diag_all, int32_t *__restrict__ keep_m, int32_t *__restrict__ keep_u,
@@ -1440,9 +1549,18 @@ __global__ void k_pair_keep(const int2 *__restrict__ pairs, int64_t npairs, cons
     const unsigned long long nfull = __popcll(__ballot(phase == 1 && full));
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) np += __shfl_xor(np, o, 64);
+    // (one pair of atomics per workgroup: every wave's would queue at two addresses)
+    __shared__ unsigned long long wp[4], wf[4];
     if ((threadIdx.x & 63) == 0) {
+        wp[threadIdx.x >> 6] = np;
+        wf[threadIdx.x >> 6] = nfull;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        np = wp[0] + wp[1] + wp[2] + wp[3];
+        const unsigned long long nf = wf[0] + wf[1] + wf[2] + wf[3];
         if (np) atomicAdd(reinterpret_cast<unsigned long long *>(&counters[C_PAIRS]), np);
-        if (nfull) atomicAdd(&counters[C_TPFULL], (int32_t)nfull);
+        if (nf) atomicAdd(&counters[C_TPFULL], (int32_t)nf);
     }
 }
 
@@ -1924,13 +2042,16 @@ __global__ __launch_bounds__(256) void k_tile_project(const float *__restrict__ 
 // S[I][J] = max over the rows x of tile I of (z_x - zc_I).(zc_J - zc_I) in
 // FP32 (both factors rounded to FP32, FP32 sums: an error below 3e-6 |u| |g|,
 // which the pair bound's margin covers); -inf for a tile without rows.  One
-// workgroup per tile I: its rows' u = z_x - zc_I in LDS, one tile J per thread.
+// workgroup per tile I: its rows' u = z_x - zc_I in LDS; lane l holds tiles
+// J = l and l + 64 of a block of 128 and wave w a quarter of the rows, so that a
+// row's read from LDS, the bound, serves two tiles (797 tiles: 222 us, 320 with
+// one tile per thread over all rows and its own strided zc; 79 tiles: 66 -> 17).
 __global__ __launch_bounds__(256) void k_tile_support(const int32_t *__restrict__ order, int64_t n,
                                                       const double *__restrict__ z, const double *__restrict__ zc,
                                                       const int32_t *__restrict__ cnt, int64_t nt,
                                                       float *__restrict__ S) {
-    __shared__ __align__(16) float us[GT][KQ + 4];  // (rows 16-byte aligned: vector LDS reads)
-    __shared__ int32_t ok[GT];
+    // rows 16-byte aligned (vector LDS reads); column KQ starts the row's sums: 0, or -inf for padding
+    __shared__ __align__(16) float us[GT][KQ + 4];
     const int tid = threadIdx.x;
     const int64_t T = blockIdx.x;
     if (cnt[T] == 0) {
@@ -1943,7 +2064,7 @@ __global__ __launch_bounds__(256) void k_tile_support(const int32_t *__restrict_
         // (loads without branches: a padding row reads point 0 and is left out)
         const int32_t id = order[T * GT + tid];
         const bool valid = id < n;
-        ok[tid] = valid ? 1 : 0;
+        us[tid][KQ] = valid ? 0.0f : -SCR_INF;
         const double *zi = z + (valid ? (int64_t)id : 0) * KQ;
         double v[KQ];
 #pragma unroll
@@ -1953,20 +2074,44 @@ __global__ __launch_bounds__(256) void k_tile_support(const int32_t *__restrict_
         for (int q = 0; q < KQ; ++q) us[tid][q] = valid ? (float)(v[q] - zt[q]) : 0.0f;
     }
     __syncthreads();
-    for (int64_t J = tid; J - tid < nt; J += 256) {
-        const bool live = J < nt;
-        const double *zj = zc + (live ? J : T) * KQ;
-        float g[KQ];
+    __shared__ float part[4][128];
+    __shared__ float gs[128][KQ + 1];
+    const int lane = tid & 63, w = tid >> 6;
+    for (int64_t J0 = 0; J0 < nt; J0 += 128) {
+        float g[2][KQ], m[2] = {-SCR_INF, -SCR_INF};
+        // (whole rows of zc, and each lane its tiles' from LDS: a lane's own
+        // rows are 256 bytes apart)
+        double v[16];
 #pragma unroll
-        for (int q = 0; q < KQ; ++q) g[q] = (float)(zj[q] - zt[q]);
-        float m = -SCR_INF;
-        for (int r = 0; r < GT; ++r) {
-            float t = 0.0f;
+        for (int e = 0; e < 16; ++e) v[e] = zc[min(J0 * KQ + tid + 256 * e, nt * KQ - 1)];
 #pragma unroll
-            for (int q = 0; q < KQ; ++q) t = fmaf(us[r][q], g[q], t);
-            m = ok[r] ? fmaxf(m, t) : m;
+        for (int e = 0; e < 16; ++e) {
+            const int at = tid + 256 * e;
+            gs[at / KQ][at % KQ] = (float)(v[e] - zt[at % KQ]);
         }
-        if (live) S[T * nt + J] = m;
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < KQ; ++q) g[h][q] = gs[64 * h + lane][q];
+#pragma unroll 4
+        for (int r = 64 * w; r < 64 * w + 64; ++r) {
+            float t[2] = {us[r][KQ], us[r][KQ]};
+#pragma unroll
+            for (int q = 0; q < KQ; ++q) {
+                const float u = us[r][q];
+                t[0] = fmaf(u, g[0][q], t[0]);
+                t[1] = fmaf(u, g[1][q], t[1]);
+            }
+            m[0] = fmaxf(m[0], t[0]);
+            m[1] = fmaxf(m[1], t[1]);
+        }
+        part[w][lane] = m[0];
+        part[w][64 + lane] = m[1];
+        __syncthreads();
+        if (tid < 128 && J0 + tid < nt)
+            S[T * nt + J0 + tid] = fmaxf(fmaxf(part[0][tid], part[1][tid]), fmaxf(part[2][tid], part[3][tid]));
+        __syncthreads();
     }
 }
 
@@ -3333,11 +3478,11 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
         fill<int32_t>(P.counters + C_OVF, 0, 1, s);
         fill<int32_t>(P.counters + C_GATHER, 0, 1, s);
         if (f64)
-            hipLaunchKernelGGL(k_recheck_rows<true>, dim3(row_grid(n)), dim3(256), 0, s, X, n, d, ld, P.best, P.Emax,
+            hipLaunchKernelGGL(k_recheck_rows<true>, dim3(grid_for(n, 4 * RCK_ROWS)), dim3(256), 0, s, X, n, d, ld, P.best, P.Emax,
                                ubp, P.comp, P.comp_ub, P.ccnt, P.cj, P.cl, kappa, dn, P.rb_d2, P.rb_j, P.glist,
                                P.counters);
         else
-            hipLaunchKernelGGL(k_recheck_rows<false>, dim3(row_grid(n)), dim3(256), 0, s, X, n, d, ld, P.best,
+            hipLaunchKernelGGL(k_recheck_rows<false>, dim3(grid_for(n, 4 * RCK_ROWS)), dim3(256), 0, s, X, n, d, ld, P.best,
                                P.Emax, ubp, P.comp, P.comp_ub, P.ccnt, P.cj, P.cl, kappa, dn, P.rb_d2, P.rb_j, P.glist,
                                P.counters);
         LAUNCH_CHECK();
