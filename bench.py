@@ -70,8 +70,9 @@ def traffic_report(fetch_dir, write_dir, precision, copy_mib):
         """Summed counter over the screen's dispatches (both phases of a round,
         diagonal and off-diagonal), the number of screened rounds, and the
         copy's value.  A screened round is a run of consecutive screen
-        dispatches of one mode (the profiled step's rounds are plain, list
-        building and final, so the mode changes at every round)."""
+        dispatches of one mode (the profiled step's rounds are list building
+        and final); the plain dispatches right before a list-building run are
+        that round's own sample, which sets the lists' first thresholds."""
         import re
         total, copy, modes = 0.0, None, []
         for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
@@ -86,7 +87,8 @@ def traffic_report(fetch_dir, write_dir, precision, copy_mib):
                 elif "copyBuffer" in r["Kernel_Name"] and copy is None and v > 0.25 * copy_mib * 1024:
                     copy = v
         modes.sort()
-        rounds = sum(1 for i, (_, md) in enumerate(modes) if i == 0 or md != modes[i - 1][1])
+        runs = [md for i, (_, md) in enumerate(modes) if i == 0 or md != modes[i - 1][1]]
+        rounds = sum(1 for i, md in enumerate(runs) if not (md == "0" and runs[i + 1:i + 2] == ["1"]))
         return total, rounds, copy
 
     ft, fr, fc = per_kernel(fetch_dir, "FETCH_SIZE")
@@ -109,7 +111,7 @@ def traffic_report(fetch_dir, write_dir, precision, copy_mib):
                "python bench.py --traffic-report <fetch_dir> <write_dir> --precision %s --calibrate-copy %d"
                % (precision, copy_mib)],
            "note": "FETCH_SIZE and WRITE_SIZE summed over the screen's dispatches of every screened round (the "
-                   "plain first round, the second round that also builds the neighbour lists, the final round; "
+                   "first round, which also builds the neighbour lists, with their sample, and the final round; "
                    "each round's two phases and its masked and unmasked dispatches) "
                    "and divided by the number of those rounds; each counter is scaled by what it reads for the "
                    "plain device copy run first in the same process (FETCH_SIZE counts half the copied bytes, "
@@ -326,8 +328,8 @@ def graph_weights_timing():
     """Full-graph vertex weights and potential (eqs. 2.2-2.3, FP64 on the
     vector units) at the blobs (n = 20,000, d = 128) and anisotropic-mixture
     (n = 50,000, d = 64) sizes: time and FP64 rate, counting 3 d flops per
-    ordered pair of points (difference, square, sum) against the 78.6 TFLOP/s
-    FP64 vector peak."""
+    unordered pair of points (difference, square, sum; each pair's distance is
+    formed once) against the 78.6 TFLOP/s FP64 vector peak."""
     import torch
 
     import paper_1702_04739_amd as iso
@@ -338,7 +340,7 @@ def graph_weights_timing():
         log("graph weights %s" % c["name"])
         X = torch.from_numpy(datagen.config(cfg)).cuda()
         ms = _timed(lambda: iso.graph_weights(X, 1.0, alpha=0.05), reps=1)
-        fl = 3.0 * c["d"] * c["n"] * (c["n"] - 1)
+        fl = 1.5 * c["d"] * c["n"] * (c["n"] - 1)
         out[c["name"]] = {"n": c["n"], "d": c["d"], "ms": ms, "fp64_tflops": fl / (ms * 1e-3) / 1e12,
                           "frac_fp64_peak": fl / (ms * 1e-3) / 78.6e12}
     return out
