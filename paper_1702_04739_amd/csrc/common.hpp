@@ -152,6 +152,13 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Waits until this wave's global stores and atomics have reached the L2.  A
+// barrier orders them within the workgroup only and need not wait for them, so
+// a device fence that one wave issues behind it for the whole workgroup (it
+// writes back the L2) covers the other waves' stores only when each has drained
+// them before the barrier.
+__device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ------------------------------------------------------------------ histogram
 
 constexpr int HIST_LDS_BINS = 4096;  // bins a workgroup counts in LDS before one global add per bin

@@ -322,8 +322,9 @@ __global__ __launch_bounds__(DB) void k_dense_round(int64_t n, int64_t nd, const
         }
     }
     // This workgroup's rows before its arrival, the others' before the reads.
-    // (One fence per workgroup, between barriers, orders all its waves; each
-    // writes back the L2: with one per wave a round of n = 2000 took 46 us, 15 so.)
+    // (One fence per workgroup, between barriers, orders all its waves once their
+    // stores have drained; each writes back the L2: with one per wave a round of n = 2000 took 46 us, 15 so.)
+    drain_stores();
     __syncthreads();
     if (tid == 0) {
         __threadfence();

@@ -401,7 +401,9 @@ __global__ __launch_bounds__(256) void k_sel_round(const double *vals, const int
     for (int b = threadIdx.x; b < SEL_BINS; b += 256)
         if (cnt[b]) atomicAdd(&st->hist[b], cnt[b]);
     // this workgroup's counts before its arrival, the others' before the reads:
-    // one fence per workgroup, between barriers (each writes back the L2)
+    // one fence per workgroup, between barriers (each writes back the L2), once
+    // every wave's atomics have drained
+    drain_stores();
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();

@@ -1350,6 +1350,7 @@ __global__ __launch_bounds__(UPPER_THREADS) void k_walk_top(WalkArgs A, int tier
                                                             int32_t *cnt_next, unsigned long long *thr_next) {
     __shared__ UpperLds L;
     if (!A.st->bad && !A.S[0].final) walk_upper(A, tier, 0, 0, 1, L);
+    drain_stores();
     __syncthreads();
     if (threadIdx.x == 0) __threadfence();  // the waves' atomics before the reads below
     __syncthreads();
