@@ -704,11 +704,12 @@ __device__ inline double cut_threshold(double num, double den) {
 // Walks the answers of the pass just run (YES: at least k cuts => beta = mid,
 // else alpha = mid), then chooses the next pass's thresholds.  One wave.  Every
 // threshold repeats the midpoint arithmetic the sequential bisection performs
-// on its way to it.
+// on its way to it.  `recorded`: the pass wrote this search's own decisions (a
+// shared pass gives every search the counts, but walks search 0 alone).
 __device__ __forceinline__ void search_step(Search *__restrict__ gS, TreeState *__restrict__ st, double *__restrict__ Nvals,
                             const int32_t *__restrict__ cnt, const unsigned long long *__restrict__ thr,
                             int32_t *__restrict__ cnt_next, unsigned long long *__restrict__ thr_next,
-                            int32_t *__restrict__ ncut, bool first) {
+                            int32_t *__restrict__ ncut, bool first, bool recorded) {
     const int lane = threadIdx.x & 63;
     Search S = *gS;
     cnt_next[lane] = 0;
@@ -729,7 +730,9 @@ __device__ __forceinline__ void search_step(Search *__restrict__ gS, TreeState *
         S.passes += 1;
         const int32_t ch = __shfl(c, HI_LANE, 64);
         if (S.mode == MODE_RECORD) {
-            S.final = 1;
+            // (a bracket that is closed from the start: the shared pass records
+            // search 0, the others record in the next one)
+            S.final = recorded ? 1 : 0;
             S.hi_cnt = ch;
         } else {
             if ((S.mode == MODE_TREE || S.mode == MODE_PATH) && ch < S.k) bad |= 16;  // beta must stay YES
@@ -1343,7 +1346,7 @@ __global__ __launch_bounds__(64) void k_walk0_top(WalkArgs A, Search *S, double 
     __shared__ u32x4 rec[Records0::NBUF * Records0::LOADS * 64];
     if (!A.st->bad && !A.S[0].final) walk_tier0(A, 0, 0, 1, stack, rec);
     __threadfence();  // this wave's atomics before the reads below
-    search_step(S, A.st, Nvals, A.cnt, A.thr, cnt_next, thr_next, A.ncut, false);
+    search_step(S, A.st, Nvals, A.cnt, A.thr, cnt_next, thr_next, A.ncut, false, true);
 }
 
 __global__ __launch_bounds__(UPPER_THREADS) void k_walk_top(WalkArgs A, int tier, Search *S, double *Nvals,
@@ -1354,7 +1357,7 @@ __global__ __launch_bounds__(UPPER_THREADS) void k_walk_top(WalkArgs A, int tier
     __syncthreads();
     if (threadIdx.x == 0) __threadfence();  // the waves' atomics before the reads below
     __syncthreads();
-    if (threadIdx.x < 64) search_step(S, A.st, Nvals, A.cnt, A.thr, cnt_next, thr_next, A.ncut, false);
+    if (threadIdx.x < 64) search_step(S, A.st, Nvals, A.cnt, A.thr, cnt_next, thr_next, A.ncut, false, true);
 }
 
 // The step alone, for the first pass and for several searches: search g reads
@@ -1364,7 +1367,7 @@ __global__ __launch_bounds__(64) void k_step(Search *S, TreeState *st, double *N
                                              unsigned long long *thr_next, int32_t *ncut, int first, int shared) {
     const int g = blockIdx.x, row = shared ? 0 : g;
     search_step(S + g, st, Nvals + g * M, cnt + row * M, thr + row * M, cnt_next + g * M, thr_next + g * M, ncut + g,
-                first != 0);
+                first != 0, !shared || g == 0);
 }
 
 // ------------------------------------------------------------------ labels (Algorithm 4)
