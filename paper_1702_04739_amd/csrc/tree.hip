@@ -1573,7 +1573,7 @@ __global__ __launch_bounds__(64) void k_final_cost(const double *__restrict__ cl
     }
     if (threadIdx.x == 0) {
         S->i_k = best;
-        S->jstar = js;
+        S->jstar = js == 0x7FFFFFFF ? 0 : js;  // (no cost above -1: the first, as where the cuts fit their list)
     }
 }
 
