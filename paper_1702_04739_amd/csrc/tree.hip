@@ -726,6 +726,7 @@ __device__ __forceinline__ void search_step(Search *__restrict__ gS, TreeState *
         S.beta = st->beta0;
         const double mid = (S.alpha + S.beta) / 2.0;
         if (mid <= S.alpha || mid >= S.beta || S.iters >= S.max_iters || !(S.beta > S.alpha)) S.done = 1;
+        if (S.alpha != S.alpha) bad |= 8;  // (weights that are no numbers: no midpoint to compare with)
     } else {
         S.passes += 1;
         const int32_t ch = __shfl(c, HI_LANE, 64);

@@ -40,3 +40,20 @@ def test_closed_bracket_all_k(orc, n, eps, bracket):
         np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
         np.testing.assert_array_equal(lab_all[k - 2].cpu().numpy(), ref.labels)
         assert abs(ik - ref.i_k) <= 1e-12 * abs(ref.i_k) and ik_all[k - 2] == ik
+
+
+def test_weights_that_are_no_numbers_are_refused():
+    """A NaN weight makes the printed lower end NaN: no bracket, hence an error and no labels, for one k and for all."""
+    import paper_1702_04739_amd as iso
+    n = 60
+    parent = np.arange(-1, n - 1, dtype=np.int32)
+    length = np.ones(n)
+    length[0] = 0.0
+    om = np.ones(n)
+    om[n // 2] = np.nan
+    pg, lg = torch.from_numpy(parent).cuda(), torch.from_numpy(length).cuda()
+    kw = dict(sigma=1.0, bracket="paper", omega0=torch.from_numpy(om).cuda())
+    with pytest.raises(iso._lib.IsoError):
+        iso.isoperimetric_subpartition(pg, lg, 3, **kw)
+    with pytest.raises(iso._lib.IsoError):
+        iso.subpartition_all_k(pg, lg, 4, **kw)
