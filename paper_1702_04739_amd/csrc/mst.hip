@@ -50,9 +50,9 @@ enum Counter : int {
     C_NONFINITE = 2,    // nonfinite coordinate seen
     C_OVF = 3,          // overflow rows this round
     C_NOEDGE = 4,       // a component without an outgoing edge (internal error)
-    // 5 unused
-    C_GATHER = 6,       // rows queued for the gathered pass this round
-    C_FORCE = 7,        // rows the neighbour lists leave undecided this round
+    C_GATHER = 5,       // rows queued for the gathered pass this round
+    C_MUTUAL = 6,       // first round's sample: rows that are their nearest row's nearest within their tile
+    C_FORCE = 7,        // rows the neighbour lists leave undecided this round (the sample: rows at the margin's limit)
     C_CAND = 8,         // candidates re-evaluated (int64 at [8..9])
     C_RESCAN = 10,      // rows rescanned (int64 at [10..11])
     C_SUMSQ = 12,       // sum over components of size^2 (int64 at [12..13], timing only)
@@ -785,10 +785,11 @@ __global__ __launch_bounds__(256) void k_rescan(const float *__restrict__ X, int
 // normal and mixture data, so no later round screens in full: n = 100,000,
 // d = 4096 sparse rows (pair bounds, which had no lists) went from five screens of
 // 26.7 ms to one, 157 -> 48.7 ms; n = 200,000, d = 784 from two to one,
-// 19.0 -> 17.0 ms.  Where the bound is too loose for lists on most rows (the
-// sample tells), below 32 tiles and with ISO_MST_NO_PRUNE (whose order has no
-// near tiles first) the second round's screen builds them, with
-// tau_i = LIST_LAMBDA b_i from the first round's minimum b_i (pair bounds: none).
+// 19.0 -> 17.0 ms.  Where the bound is too loose for lists on most rows or the
+// first round will join nearly all points (the sample tells both), below 32
+// tiles and with ISO_MST_NO_PRUNE (whose order has no near tiles first) the
+// second round's screen builds them, with tau_i = LIST_LAMBDA b_i from the first
+// round's minimum b_i (pair bounds: none).
 
 constexpr float LIST_LAMBDA = 1.1f;
 // The first round's lists, measured at n = 100,000, d = 4096 (sparse rows) and
@@ -800,6 +801,16 @@ constexpr float LIST_LAMBDA = 1.1f;
 constexpr int LIST_SLOTS = 4;    // sampled minima per row
 constexpr int LIST_KEEP = 16;    // entries that set a row's next tau
 constexpr int LIST_MOST = 64;    // most entries a trimmed list keeps
+// Where nearly every point's nearest point has a nearer one still (heavy-tailed
+// norms: the next one inwards), the first round leaves next to no components and
+// lists are built for nothing, by a screen that takes up to 1.7 times a plain
+// one.  A round leaves as many components as there are pairs of mutually nearest
+// points, and the share of such pairs within tiles tells: lists want one row in
+// LIST_MUTUAL in such a pair.  Share of the rows, own tiles: lognormal radii
+// (sigma 0.25 to 1.5, d = 64 and 784) 0.8 to 3.5 %; sparse rows 8 to 9 %, lognormal
+// coordinates 12 to 19 %, normal points, images, mixtures 16 to 30 %, planes 60 %.  n = 50,000, d = 64, sigma 1:
+// 6.4 ms with lists, 3.5 without; sparse rows, n = 20,000: 5.1 with, 11.6 without.
+constexpr int LIST_MUTUAL = 16;
 constexpr int LIST_FIRST = 2;    // the first share of the tile pairs, per tile (5 tiles seen by every row)
 constexpr double FR_EVAL_PER_POINT = 16.0;  // final round: most exact evaluations per point on average
 
@@ -834,17 +845,19 @@ __global__ void k_sample_labels(int64_t npos, int32_t *__restrict__ out) {
 // beyond it the bound is too loose for lists, and such a tau would list most
 // points of the first share.  Rows at that limit are counted in
 // counters[C_FORCE].  The least minimum starts the running one: it is the value
-// of a real pair.  (Minima over the tiles 1 .. 5 away instead of halves of the
-// own one, third smallest of six: where near tiles hold small clusters, tau
+// of a real pair.  Two rows with the same least minimum are each other's nearest
+// (a pair's value is formed once and merged into both): counted in
+// counters[C_MUTUAL].  One workgroup per tile.  (Minima over the tiles 1 .. 5
+// away instead of halves of the own one, third smallest of six: where near tiles hold small clusters, tau
 // reached other clusters and lists overflowed; n = 50,000, d = 16 in clusters
 // of 300: 11.4 ms, 5.9 so, 7.1 with the second round's lists.)
-__global__ void k_list_tau(const int32_t *__restrict__ order, int64_t npos, int64_t n, const float *__restrict__ smp,
+__global__ __launch_bounds__(GT) void k_list_tau(const int32_t *__restrict__ order, int64_t npos, int64_t n,
+                           const float *__restrict__ smp,
                            const float *__restrict__ smp_ub, float margin, const float *__restrict__ pEmax,
                            float *__restrict__ ltau, float *__restrict__ pltau, int32_t *__restrict__ lcnt,
                            uint32_t *__restrict__ ldrop, float *__restrict__ pbest, float *__restrict__ pub,
                            int32_t *__restrict__ counters) {
-    const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos >= npos) return;  // (whole tiles: no wave is cut)
+    const int64_t pos = (int64_t)blockIdx.x * GT + threadIdx.x;
     const int32_t id = order[pos];
     float lo = SCR_INF, lou = SCR_INF, top = -1.0f, topu = -1.0f;
 #pragma unroll
@@ -863,6 +876,14 @@ __global__ void k_list_tau(const int32_t *__restrict__ order, int64_t npos, int6
     const float tau = id < n && top >= 0.0f ? fminf(fminf(far, top * margin), FLT_MAX) : -1.0f;
     const int loose = __popcll(__ballot(tau >= 0.0f && far > top * margin));
     if ((threadIdx.x & 63) == 0 && loose) atomicAdd(&counters[C_FORCE], loose);
+    __shared__ uint32_t least[GT];
+    least[threadIdx.x] = id < n && lo < SCR_INF ? __float_as_uint(lo) : 0x80000000u | threadIdx.x;
+    __syncthreads();
+    int same = 0;
+#pragma unroll 16
+    for (int q = 0; q < GT; ++q) same += least[q] == least[threadIdx.x] ? 1 : 0;
+    const int mutual = __popcll(__ballot(same > 1));
+    if ((threadIdx.x & 63) == 0 && mutual) atomicAdd(&counters[C_MUTUAL], mutual);
     pltau[pos] = tau;
     if (id < n) {
         ltau[id] = tau;
@@ -3049,7 +3070,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
     // The thresholds of the first round's lists (k_list_tau), from LIST_SLOTS
     // screens of the diagonal tile pairs, whose labels and minima go to the
     // list arrays, not yet in use.  False, and no lists, where the bound is too
-    // loose for most rows.
+    // loose for most rows or this round will join nearly all points.
     auto sample_lists = [&]() -> bool {
         static_assert((1 << LIST_SLOTS) <= GT && 2 * LIST_SLOTS < LIST_CAP, "sampled minima");
         float *const smp = P.lv, *const smp_ub = pb ? P.lv + LIST_SLOTS * P.n_pad : nullptr;
@@ -3073,13 +3094,14 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
         SA.kappa = with;
         SA.pbest = P.pbest;
         SA.pub = pb ? P.pub : nullptr;
-        hipLaunchKernelGGL(k_list_tau, dim3(grid_for(P.n_pad, 256)), dim3(256), 0, s, P.perm, P.n_pad, n, smp, smp_ub,
+        hipLaunchKernelGGL(k_list_tau, dim3((unsigned)(P.n_pad / GT)), dim3(GT), 0, s, P.perm, P.n_pad, n, smp, smp_ub,
                            1.0f + std::max(1.0f / 32.0f, 6.0f / (float)d), P.pEmax, P.ltau, P.pltau, P.lscnt, P.ldrop, P.pbest, P.pub, P.counters);
         LAUNCH_CHECK();
-        int32_t loose = 0;
-        R.get(&loose, P.counters + C_FORCE, sizeof(int32_t), s);
+        static_assert(C_FORCE == C_MUTUAL + 1, "read together");
+        int32_t h[2] = {0, 0};  // mutual, loose
+        R.get(h, P.counters + C_MUTUAL, sizeof(h), s);
         R.sync(s);
-        if (2 * (int64_t)loose > n) return false;
+        if (2 * (int64_t)h[1] > n || LIST_MUTUAL * (int64_t)h[0] < n) return false;
         SA.ltau = P.ltau;
         SA.lcnt = P.lscnt;
         SA.ldrop = P.ldrop;

@@ -47,3 +47,9 @@ def _same_tree(iso, X, lists, **kw):
 def test_rows_without_a_listed_bound(iso, n, frac, mu, sigma, recheck):
     """A component far out whose rows list only each other: every row is undecided and has no bound yet."""
     _same_tree(iso, _tails(n, 64, frac, mu, sigma, n), True, precision="bf16", recheck=recheck)
+
+
+@pytest.mark.parametrize("n,sigma", [(8200, 0.25), (20000, 0.5), (50000, 1.0)])
+def test_no_lists_where_the_first_round_joins_nearly_all(iso, n, sigma):
+    """Every point's nearest point lies further inwards: next to no pairs of mutually nearest points."""
+    _same_tree(iso, _tails(n, 64, 1.0, 0.0, sigma, n), False, precision="bf16", pair_bounds=True)
