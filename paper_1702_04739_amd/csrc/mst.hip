@@ -1012,6 +1012,7 @@ __global__ __launch_bounds__(256) void k_list_capture(
     const uint32_t *__restrict__ ldrop, const int32_t *__restrict__ lj, const float *__restrict__ lv, float kappa, float dn, int32_t *__restrict__ ccnt,
     int32_t *__restrict__ cj, float *__restrict__ cl, int32_t *__restrict__ counters) {
     const int lane = threadIdx.x & 63;
+    int forced = 0, unbounded = 0;  // lane 0's (one atomic per wave: thousands of rows may be undecided)
     for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
         const int ci = comp[i];
         const float b = best[i], E = Emax[i];
@@ -1022,8 +1023,8 @@ __global__ __launch_bounds__(256) void k_list_capture(
         if (!(thr < SCR_INF) || !((ub ? t : lower_of(t, E)) > thr)) {
             if (lane == 0) {
                 ccnt[i] = SCR_FORCE;
-                atomicAdd(&counters[C_FORCE], 1);
-                if (!(b < SCR_INF)) atomicAdd(&counters[C_UNBOUND], 1);
+                ++forced;
+                if (!(b < SCR_INF)) ++unbounded;
             }
             continue;
         }
@@ -1053,6 +1054,8 @@ __global__ __launch_bounds__(256) void k_list_capture(
         }
         if (lane == 0) ccnt[i] = taken > SCR_CAP ? SCR_CAP + 1 : taken;
     }
+    if (forced) atomicAdd(&counters[C_FORCE], forced);
+    if (unbounded) atomicAdd(&counters[C_UNBOUND], unbounded);
 }
 
 // ------------------------------------------------------------------ final round
