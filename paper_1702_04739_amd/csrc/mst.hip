@@ -813,6 +813,7 @@ constexpr int LIST_MOST = 64;    // most entries a trimmed list keeps
 // 6.4 ms with lists, 3.5 without; sparse rows, n = 20,000: 5.1 with, 11.6 without.
 constexpr int LIST_MUTUAL = 16;
 constexpr int LIST_UNBOUND = 64;  // see the gathered pass of a list round
+constexpr int LIST_FLOOD = 4 * LIST_CAP;  // of the at most 1,280 points that the first share shows a row
 constexpr int LIST_FIRST = 2;    // the first share of the tile pairs, per tile (5 tiles seen by every row)
 constexpr double FR_EVAL_PER_POINT = 16.0;  // final round: most exact evaluations per point on average
 
@@ -875,8 +876,10 @@ __global__ __launch_bounds__(GT) void k_list_tau(const int32_t *__restrict__ ord
     if (smp_ub) pub[pos] = lou;
     const float far = (smp_ub ? topu : top + 2.0f * pEmax[pos]) * (1.0f + 0x1p-10f);
     // (finite: no padding, whose value is +inf, is listed; a row without a minimum keeps no list)
-    const float tau = id < n && top >= 0.0f ? fminf(fminf(far, top * margin), FLT_MAX) : -1.0f;
-    const int loose = __popcll(__ballot(tau >= 0.0f && far > top * margin));
+    const bool bounded = id < n && top >= 0.0f;
+    float tau = bounded ? fminf(fminf(far, top * margin), FLT_MAX) : -1.0f;
+    if (tau <= (smp_ub ? 0.0f : pEmax[pos])) tau = -1.0f;  // (decides nothing: see k_list_trim)
+    const int loose = __popcll(__ballot(bounded && far > top * margin));
     if ((threadIdx.x & 63) == 0 && loose) atomicAdd(&counters[C_FORCE], loose);
     __shared__ uint32_t least[GT];
     least[threadIdx.x] = id < n && lo < SCR_INF ? __float_as_uint(lo) : 0x80000000u | threadIdx.x;
@@ -914,19 +917,25 @@ __device__ __forceinline__ uint32_t kth_smallest(uint32_t a, uint32_t b, int k) 
 // One wave per position: a list of more than LIST_KEEP entries is cut to those
 // at or below a lower tau: the LIST_KEEP-th smallest value plus the margin a
 // decision needs (2 Emax; pair bounds: the LIST_KEEP-th smallest upper bound
-// lb + 2 E_ij), but no more than LIST_MOST entries.
+// lb + 2 E_ij), but no more than LIST_MOST entries.  A row that was offered
+// LIST_FLOOD entries or more in the share has that many equal or nearly equal
+// distances: its tau drops below the smallest dropped value, which bounds the row
+// anyway, so that it stops offering them.  A list whose tau does not exceed Emax
+// (pair bounds: 0) decides nothing, since its lower bound is at most 0: tau -1, no
+// list.  (n = 30,000, half of them copies of one point: 116 ms without these two
+// rules, where each pair of copies costs two atomics; 87 so, 88 without lists.)
 __global__ __launch_bounds__(256) void k_list_trim(const int32_t *__restrict__ order, int64_t npos, int64_t n,
                                                    const float *__restrict__ Emax, const float *__restrict__ rn,
                                                    const float *__restrict__ re, ScreenBound bound, int pb,
                                                    float *__restrict__ ltau, float *__restrict__ pltau,
-                                                   int32_t *__restrict__ lcnt, int32_t *__restrict__ lj,
-                                                   float *__restrict__ lv) {
+                                                   int32_t *__restrict__ lcnt, const uint32_t *__restrict__ ldrop,
+                                                   int32_t *__restrict__ lj, float *__restrict__ lv) {
     static_assert(LIST_CAP == 128, "two entries per lane");
     const int lane = threadIdx.x & 63;
     for (int64_t pos = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); pos < npos; pos += (int64_t)gridDim.x * 4) {
         const int64_t i = order[pos];
         if (i >= n) continue;
-        const int cnt = min(lcnt[i], LIST_CAP);
+        const int offered = lcnt[i], cnt = min(offered, LIST_CAP);
         if (cnt <= LIST_KEEP) continue;
         int32_t j[2];
         uint32_t v[2], u[2];
@@ -945,11 +954,13 @@ __global__ __launch_bounds__(256) void k_list_trim(const int32_t *__restrict__ o
         float tau = (pb ? kth : kth + 2.0f * Emax[i]) * (1.0f + 0x1p-10f);
         if (count_le(v[0], v[1], __float_as_uint(tau)) > LIST_MOST)
             tau = __uint_as_float(kth_smallest(v[0], v[1], LIST_MOST));
+        if (offered >= LIST_FLOOD) tau = fminf(tau, __uint_as_float(max(ldrop[i], 1u) - 1u));
+        if (tau <= (pb ? 0.0f : Emax[i])) tau = -1.0f;
         if (!(tau < ltau[i])) continue;
         int kept = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const bool in = v[h] <= __float_as_uint(tau);
+            const bool in = tau >= 0.0f && v[h] <= __float_as_uint(tau);
             const unsigned long long bal = __ballot(in);
             const int at = kept + __popcll(bal & ((1ull << lane) - 1ull));
             if (in) {
@@ -3451,7 +3462,7 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
                 auto share = [&](int64_t masked) {
                     launch_screen_pairs(SA, masked ? pairs_use : pairs_use + nmask + at, masked, end - at, s);
                     hipLaunchKernelGGL(k_list_trim, dim3(row_grid(P.n_pad)), dim3(256), 0, s, P.perm, P.n_pad, n, P.Emax,
-                                       P.rn, P.re, bound, pb ? 1 : 0, P.ltau, P.pltau, P.lscnt, P.lj, P.lv);
+                                       P.rn, P.re, bound, pb ? 1 : 0, P.ltau, P.pltau, P.lscnt, P.ldrop, P.lj, P.lv);
                     LAUNCH_CHECK();
                 };
                 share(nmask);

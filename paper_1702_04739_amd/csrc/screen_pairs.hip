@@ -219,7 +219,7 @@ __device__ __forceinline__ void list_push_global(const ScreenArgs &A, int64_t p,
     if (pos < LIST_CAP) {
         A.lj[p * LIST_CAP + pos] = other;
         A.lv[p * LIST_CAP + pos] = v;
-    } else {
+    } else if (__float_as_uint(v) < *(const volatile uint32_t *)&A.ldrop[p]) {  // (an older value can only be larger)
         atomicMin(&A.ldrop[p], __float_as_uint(v));
     }
 }

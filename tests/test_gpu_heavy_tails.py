@@ -53,3 +53,18 @@ def test_rows_without_a_listed_bound(iso, n, frac, mu, sigma, recheck):
 def test_no_lists_where_the_first_round_joins_nearly_all(iso, n, sigma):
     """Every point's nearest point lies further inwards: next to no pairs of mutually nearest points."""
     _same_tree(iso, _tails(n, 64, 1.0, 0.0, sigma, n), False, precision="bf16", pair_bounds=True)
+
+
+def _half_copies(n, d, spread, seed):
+    """Half of the points at one place: copies, or as near as `spread`."""
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, d))
+    X[: n // 2] = 0.37 + spread * X[: n // 2]
+    return X[rng.permutation(n)].astype(np.float32)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("n,d,spread", [(8200, 16, 0.0), (9001, 33, 1e-6), (12000, 8, 1e-3)])
+def test_rows_that_flood_their_list(iso, n, d, spread, precision):
+    """More (nearly) equal distances in a tile than a list is offered before it is cut to below its dropped values."""
+    _same_tree(iso, _half_copies(n, d, spread, n), None, precision=precision)
