@@ -52,7 +52,6 @@ enum Counter : int {
     C_NOEDGE = 4,       // a component without an outgoing edge (internal error)
     C_GATHER = 5,       // rows queued for the gathered pass this round
     C_MUTUAL = 6,       // first round's sample: rows that are their nearest row's nearest within their tile
-    C_UNBOUND = 6,      // list rounds: undecided rows without a listed point of another component
     C_FORCE = 7,        // rows the neighbour lists leave undecided this round (the sample: rows at the margin's limit)
     C_CAND = 8,         // candidates re-evaluated (int64 at [8..9])
     C_RESCAN = 10,      // rows rescanned (int64 at [10..11])
@@ -812,7 +811,6 @@ constexpr int LIST_MOST = 64;    // most entries a trimmed list keeps
 // coordinates 12 to 19 %, normal points, images, mixtures 16 to 30 %, planes 60 %.  n = 50,000, d = 64, sigma 1:
 // 6.4 ms with lists, 3.5 without; sparse rows, n = 20,000: 5.1 with, 11.6 without.
 constexpr int LIST_MUTUAL = 16;
-constexpr int LIST_UNBOUND = 64;  // see the gathered pass of a list round
 constexpr int LIST_FLOOD = 4 * LIST_CAP;  // of the at most 1,280 points that the first share shows a row
 constexpr int LIST_FIRST = 2;    // the first share of the tile pairs, per tile (5 tiles seen by every row)
 constexpr double FR_EVAL_PER_POINT = 16.0;  // final round: most exact evaluations per point on average
@@ -1023,7 +1021,7 @@ __global__ __launch_bounds__(256) void k_list_capture(
     const uint32_t *__restrict__ ldrop, const int32_t *__restrict__ lj, const float *__restrict__ lv, float kappa, float dn, int32_t *__restrict__ ccnt,
     int32_t *__restrict__ cj, float *__restrict__ cl, int32_t *__restrict__ counters) {
     const int lane = threadIdx.x & 63;
-    int forced = 0, unbounded = 0;  // lane 0's (one atomic per wave: thousands of rows may be undecided)
+    int forced = 0;  // lane 0's (one atomic per wave: thousands of rows may be undecided)
     for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
         const int ci = comp[i];
         const float b = best[i], E = Emax[i];
@@ -1035,7 +1033,6 @@ __global__ __launch_bounds__(256) void k_list_capture(
             if (lane == 0) {
                 ccnt[i] = SCR_FORCE;
                 ++forced;
-                if (!(b < SCR_INF)) ++unbounded;
             }
             continue;
         }
@@ -1066,7 +1063,6 @@ __global__ __launch_bounds__(256) void k_list_capture(
         if (lane == 0) ccnt[i] = taken > SCR_CAP ? SCR_CAP + 1 : taken;
     }
     if (forced) atomicAdd(&counters[C_FORCE], forced);
-    if (unbounded) atomicAdd(&counters[C_UNBOUND], unbounded);
 }
 
 // ------------------------------------------------------------------ final round
@@ -3363,7 +3359,6 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
         // Once there are lists, rows are first decided by them; the round
         // screens only when too many rows stay undecided.
         bool list_round = false;
-        int32_t unbounded = 0;  // of its undecided rows
         if (lists == LISTS_READY) {
             hipLaunchKernelGGL(k_list_best, dim3(row_grid(n)), dim3(256), 0, s, n, P.comp, P.lscnt, P.lj, P.lv, P.rn,
                                P.re, bound, P.best, ubp);
@@ -3372,17 +3367,14 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
             hipLaunchKernelGGL(k_comp_ub, dim3(grid_for(P.n_pad, 256)), dim3(256), 0, s, P.perm, P.n_pad, P.best,
                                P.Emax, ubp, P.comp, n, up, P.comp_ub);
             LAUNCH_CHECK();
-            fill<int32_t>(P.counters + C_UNBOUND, 0, 2, s);
+            fill<int32_t>(P.counters + C_FORCE, 0, 1, s);
             hipLaunchKernelGGL(k_list_capture, dim3(row_grid(n)), dim3(256), 0, s, n, P.comp, P.comp_ub, P.best,
                                ubp, P.Emax, P.rn, P.re, bound, P.ltau, P.lscnt, P.ldrop, P.lj, P.lv, kappa, dn, P.ccnt, P.cj,
                                P.cl, P.counters);
             LAUNCH_CHECK();
-            static_assert(C_FORCE == C_UNBOUND + 1, "read together");
-            int32_t hu[2] = {0, 0};
-            R.get(hu, P.counters + C_UNBOUND, sizeof(hu), s);
+            int32_t h_force = 0;
+            R.get(&h_force, P.counters + C_FORCE, sizeof(int32_t), s);
             R.sync(s);
-            const int32_t h_force = hu[1];
-            unbounded = hu[0];
             // an undecided row costs a row sweep over all points, a screen
             // round about half of one per row: lists pay below ~1/6 undecided
             if ((double)h_force <= 0.15 * (double)n) {
@@ -3567,31 +3559,22 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
                                        kappa, dn, P.rb_d2, P.rb_j, P.rlist, P.counters);
                 LAUNCH_CHECK();
             };
-            // A row whose list holds no point of another component enters without
-            // a bound, and the pass's column blocks run at once, each from its own
-            // minima, which with pair bounds too many candidates pass: such rows
-            // overflow and are left to the exact rescan.  So the minima come first,
-            // by a pass that captures nothing (kappa < 0), or, for the few rows up
-            // to LIST_UNBOUND, which seldom need it, the pass runs once more from
-            // the minima it leaves if rows overflowed.  n = 50,000, d = 64, 2 % of
-            // the points far out, 172 such rows: 7.2 ms without either, 5.8 by the
-            // second pass, 4.8 by the first; at lognormal radii 6,519 rows
-            // overflowed and the call started again in FP32, 80 ms, 6.4 so.  Sparse
-            // rows, n = 20,000, d = 4096, 5 to 50 such rows: 5.1, and 5.4 with a
-            // first pass in every round.
-            if (list_round && pb && unbounded > LIST_UNBOUND) {
-                const float with = SA.kappa;
-                SA.kappa = -1.0f;
-                fill<int32_t>(P.gcnt, 0, h_gather, s);
-                screen(true);
-                SA.kappa = with;
-            }
             gather();
             if (may_escalate || (list_round && pb)) {
                 int32_t h_ovf = 0;
                 R.get(&h_ovf, P.counters + C_OVF, sizeof(int32_t), s);
                 R.sync(s);
-                if (list_round && h_ovf > 0 && unbounded > 0 && unbounded <= LIST_UNBOUND) {
+                if (list_round && h_ovf > 0) {
+                    // A row whose list holds no point of another component enters
+                    // without a bound, and the pass's column blocks run at once,
+                    // each from its own minima, which with pair bounds too many
+                    // candidates pass.  The minima are exact now: once more from
+                    // them, before rows are left to the exact rescan.  n = 50,000,
+                    // d = 64, 2 % of the points far out, 172 such rows: 7.2 ms, 4.9
+                    // so, and 4.8 with a pass for the minima ahead of every such
+                    // one, which costs the sparse rows (d = 4096, no overflow) 6 %.
+                    // More rows than that start the call again in FP32 (80 ms for
+                    // 6,519 of 50,000).
                     fill<int32_t>(P.counters + C_OVF, 0, 1, s);
                     gather();
                     R.get(&h_ovf, P.counters + C_OVF, sizeof(int32_t), s);
