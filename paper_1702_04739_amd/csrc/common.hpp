@@ -35,6 +35,7 @@ struct Fail {
         hipError_t e_ = (expr);                                                                     \
         if (e_ != hipSuccess) {                                                                     \
             ::iso::set_error("%s failed: %s (%s:%d)", #expr, hipGetErrorString(e_), __FILE__, __LINE__); \
+            (void)hipGetLastError(); /* not left for the next call's launch check */                    \
             throw ::iso::Fail{e_ == hipErrorOutOfMemory ? ISO_ERR_OOM : ISO_ERR_HIP};               \
         }                                                                                           \
     } while (0)
