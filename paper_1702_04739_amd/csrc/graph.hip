@@ -30,8 +30,8 @@ constexpr int GW_K = 16;           // coordinates per LDS stage
 constexpr int GW_R = 4;            // elements per thread and direction of a distance tile
 constexpr int GW_T = 16 * GW_R;    // rows and columns of a distance tile; W is a multiple of it
 // W is at most 4096 points: the buffer (W^2 doubles, 134 MB) then stays in the
-// 256 MB last-level cache between the two kernels, and it is never larger than
-// n * GW_BUF doubles.  At n = 50,000, d = 64 the sums take 6.1 ms with it,
+// 256 MB last-level cache between the two kernels.  W is at most 2048 or W^2 at
+// most n * GW_BUF doubles.  At n = 50,000, d = 64 the sums take 6.1 ms with it,
 // against 10.7 ms with W = 6272 (315 MB); with W = 2048 the 256 workgroups of
 // a pair's sums leave the CUs waiting on the exponentials' latency (10.6 ms).
 constexpr int64_t GW_BUF = 1024, GW_WMAX = 4096;
@@ -274,8 +274,7 @@ extern "C" iso_status iso_graph_weights(const float *X, int64_t n, int64_t d, in
         auto width = [&](int64_t g) { return (n + g * GW_T - 1) / (g * GW_T) * GW_T; };
         int64_t G = 1;
         while (width(G) > GW_WMAX || (width(G) > 2048 && width(G) * width(G) > n * GW_BUF)) ++G;
-        const int64_t W = width(G);
-        G = (n + W - 1) / W;
+        int64_t W = width(G);
         // the buffer: allocated and released in stream order (no synchronisation)
         struct StreamBuffer {
             void *p = nullptr;
@@ -285,7 +284,16 @@ extern "C" iso_status iso_graph_weights(const float *X, int64_t n, int64_t d, in
             }
         } buf;
         buf.s = s;
-        HIP_CHECK(hipMallocAsync(&buf.p, sizeof(double) * (size_t)(W * W), s));
+        // (where there is no room for it, smaller blocks: the sums are the same for any W)
+        hipError_t e = hipMallocAsync(&buf.p, sizeof(double) * (size_t)(W * W), s);
+        while (e == hipErrorOutOfMemory && W > GW_T) {
+            (void)hipGetLastError();
+            W = (W / 2 + GW_T - 1) / GW_T * GW_T;
+            e = hipMallocAsync(&buf.p, sizeof(double) * (size_t)(W * W), s);
+        }
+        if (e != hipSuccess) buf.p = nullptr;
+        HIP_CHECK(e);
+        G = (n + W - 1) / W;
         double *Dt = static_cast<double *>(buf.p);
         for (int64_t B = 0; B < G; ++B) {
             for (int64_t A = 0; A <= B; ++A) {

@@ -3834,8 +3834,16 @@ extern "C" iso_status iso_mst(const float *X, int64_t n, int64_t d, int64_t ld, 
         ScopedWorkspace owned;
         if (ws == nullptr) {
             owned.stream = s;
+            // (where there is no room for the distance matrix, the screened rounds)
             ws_bytes = std::max(need, dense);
-            HIP_CHECK(hipMallocAsync(&owned.ptr, ws_bytes, s));
+            hipError_t e = hipMallocAsync(&owned.ptr, ws_bytes, s);
+            if (e == hipErrorOutOfMemory && ws_bytes > need) {
+                (void)hipGetLastError();
+                ws_bytes = need;
+                e = hipMallocAsync(&owned.ptr, ws_bytes, s);
+            }
+            if (e != hipSuccess) owned.ptr = nullptr;
+            HIP_CHECK(e);
             ws = owned.ptr;
         }
         ISO_REQUIRE(ws_bytes >= need, ISO_ERR_WORKSPACE, "workspace %zu bytes < required %zu", ws_bytes, need);

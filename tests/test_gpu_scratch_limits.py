@@ -1,7 +1,10 @@
 """GPU: calls that allocate their own scratch where there is little room.
 
 A memory pool of limited size stands for a device that other programs fill.
-A call whose scratch does not fit is refused, and the next one is as before."""
+The tree of few points takes the screened rounds where the distance matrix does
+not fit, and the full-graph weights take smaller blocks; the results are the
+ones with room, bit for bit.  Where even that does not fit: out of memory, and
+the next call is as before."""
 import ctypes
 
 import numpy as np
@@ -65,3 +68,32 @@ def test_a_refused_call_leaves_no_error_behind():
     p1, l1, _ = _mst(X, "fp32")
     np.testing.assert_array_equal(p1, p0)
     np.testing.assert_array_equal(l1, l0)
+
+
+@pytest.mark.parametrize("recheck", ["fp32", "fp64"])
+def test_tree_without_room_for_the_matrix(recheck):
+    from paper_1702_04739_amd._lib import IsoError
+    X = torch.from_numpy(np.random.default_rng(1).standard_normal((4096, 16)).astype(np.float32)).cuda()
+    p0, l0, i0 = _mst(X, recheck)
+    assert i0.tile_pairs == 0
+    with _Room(60 << 20):
+        p1, l1, i1 = _mst(X, recheck)
+    assert i1.tile_pairs > 0
+    np.testing.assert_array_equal(p1, p0)
+    np.testing.assert_array_equal(l1, l0)
+    with _Room(16 << 20), pytest.raises(IsoError):
+        _mst(X, recheck)
+    p2, l2, i2 = _mst(X, recheck)
+    assert i2.tile_pairs == 0
+    np.testing.assert_array_equal(p2, p0)
+
+
+@pytest.mark.parametrize("n,limit", [(2000, 24 << 20), (5000, 24 << 20), (777, 1 << 20)])
+def test_graph_weights_in_smaller_blocks(n, limit):
+    import paper_1702_04739_amd as iso
+    X = torch.from_numpy(np.random.default_rng(n).standard_normal((n, 9)).astype(np.float32)).cuda()
+    om0, p0 = iso.graph_weights(X, 1.3, alpha=0.05)
+    with _Room(limit):
+        om1, p1 = iso.graph_weights(X, 1.3, alpha=0.05)
+        torch.cuda.synchronize()
+    assert torch.equal(om1, om0) and torch.equal(p1, p0)
