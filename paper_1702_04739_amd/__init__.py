@@ -70,7 +70,10 @@ def mst(points, precision: str = "fp32", recheck: str = "fp32", lists: bool = Tr
     need = ctypes.c_size_t(0)
     _lib.check(lib.iso_mst_workspace_size(n, d, _lib.PRECISION[precision], ctypes.byref(need)), "iso_mst_workspace_size")
     dev = points.device
-    ws = torch.empty(max(int(need.value), 1), dtype=torch.uint8, device=dev)
+    try:
+        ws = torch.empty(max(int(need.value), 1), dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:
+        ws = None  # the library allocates what this call needs at least
     parent = torch.empty(n, dtype=torch.int32, device=dev)
     length = torch.empty(n, dtype=torch.float64, device=dev)
     info = _lib.MstInfo()
@@ -80,7 +83,8 @@ def mst(points, precision: str = "fp32", recheck: str = "fp32", lists: bool = Tr
     rc = lib.iso_mst(ctypes.c_void_p(points.data_ptr()), n, d, ld, _lib.PRECISION[precision], _lib.RECHECK[recheck],
                      flags,
                      ctypes.c_void_p(parent.data_ptr()), ctypes.c_void_p(length.data_ptr()), ctypes.byref(info),
-                     ctypes.c_void_p(ws.data_ptr()), int(need.value), _stream_ptr(dev))
+                     ctypes.c_void_p(ws.data_ptr() if ws is not None else 0), int(need.value) if ws is not None else 0,
+                     _stream_ptr(dev))
     _lib.check(rc, "iso_mst")
     return parent, length, {"rounds": info.rounds, "list_rounds": info.list_rounds, "candidates": info.candidates,
                             "rescanned_rows": info.rescanned_rows, "mst_weight": info.mst_weight,

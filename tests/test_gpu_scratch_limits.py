@@ -97,3 +97,22 @@ def test_graph_weights_in_smaller_blocks(n, limit):
         om1, p1 = iso.graph_weights(X, 1.3, alpha=0.05)
         torch.cuda.synchronize()
     assert torch.equal(om1, om0) and torch.equal(p1, p0)
+
+
+def test_tree_where_torch_has_no_room():
+    """torch's allocator, which the Python call asks first, limited to 40 MiB beyond what it holds."""
+    import paper_1702_04739_amd as iso
+    X = torch.from_numpy(np.random.default_rng(3).standard_normal((4096, 16)).astype(np.float32)).cuda()
+    p0, l0, i0 = iso.mst(X)
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(X.device).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (40 << 20)) / total)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(134 << 20, dtype=torch.uint8, device="cuda")
+        with _Room(60 << 20):
+            p1, l1, i1 = iso.mst(X)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert i0["tile_pairs"] == 0 and i1["tile_pairs"] > 0
+    assert torch.equal(p1, p0) and torch.equal(l1, l0)
