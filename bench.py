@@ -67,14 +67,13 @@ def traffic_report(fetch_dir, write_dir, precision, copy_mib):
     prefix = "k_screen_pairs<%d, " % {"fp32": 0, "bf16": 1, "fp8": 2, "int8": 3}[precision]
 
     def per_kernel(d, counter):
-        """Summed counter over the screen's dispatches (both phases of a round,
-        diagonal and off-diagonal), the number of screened rounds, and the
-        copy's value.  A screened round is a run of consecutive screen
-        dispatches of one mode (the profiled step's rounds are list building
-        and final); the plain dispatches right before a list-building run are
-        that round's own sample, which sets the lists' first thresholds."""
-        import re
-        total, copy, modes = 0.0, None, []
+        """Summed counter over the screen's dispatches, the number of screened
+        rounds, and the copy's value.  A round's screen (both phases, masked and
+        unmasked, the sample of the neighbour lists if it takes one) is what is
+        dispatched before the round's recheck, so a round is a recheck with
+        screen dispatches since the one before; rounds that the lists decide
+        have none."""
+        total, copy, order = 0.0, None, []
         for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
             for r in csv.DictReader(open(f)):
                 if r["Counter_Name"] != counter:
@@ -82,13 +81,13 @@ def traffic_report(fetch_dir, write_dir, precision, copy_mib):
                 v = float(r["Counter_Value"])
                 if prefix in r["Kernel_Name"]:
                     total += v
-                    m = re.search(r"k_screen_pairs<\d+, \w+, (\d+)", r["Kernel_Name"])
-                    modes.append((int(r["Dispatch_Id"]), m.group(1) if m else "?"))
+                    order.append((int(r["Dispatch_Id"]), "screen"))
+                elif "k_recheck_rows" in r["Kernel_Name"] or "k_fr_recheck" in r["Kernel_Name"]:
+                    order.append((int(r["Dispatch_Id"]), "recheck"))
                 elif "copyBuffer" in r["Kernel_Name"] and copy is None and v > 0.25 * copy_mib * 1024:
                     copy = v
-        modes.sort()
-        runs = [md for i, (_, md) in enumerate(modes) if i == 0 or md != modes[i - 1][1]]
-        rounds = sum(1 for i, md in enumerate(runs) if not (md == "0" and runs[i + 1:i + 2] == ["1"]))
+        order.sort()
+        rounds = sum(1 for (_, k), (_, nk) in zip(order, order[1:]) if (k, nk) == ("screen", "recheck"))
         return total, rounds, copy
 
     ft, fr, fc = per_kernel(fetch_dir, "FETCH_SIZE")
