@@ -978,9 +978,9 @@ __global__ __launch_bounds__(256) void k_list_trim(const int32_t *__restrict__ o
 // One wave per row: b_i = min over the list's entries in other components of
 // their Dhat^2 (an upper bound of the row's minimum; +inf without such
 // entries).  With pair bounds (ub != nullptr) of their lower bounds, and ub_i
-// the least lb + 2 E_ij: lb = (Dhat^2 - E) less 2^-21 (Dhat^2 + E), or 0 when that
-// is negative, so Dhat^2 + E <= (lb + 2 E) (1 + 2^-20), and the 2^-18 covers
-// this evaluation's roundings too.
+// the least lb + 2 E_ij: lb = (Dhat^2 - E) less 2^-21 (Dhat^2 + E) (at most FLT_MAX),
+// or 0 when that is negative, so Dhat^2 + E <= (lb + 2 E) (1 + 2^-20), and the
+// 2^-18 covers this evaluation's roundings too.
 __global__ __launch_bounds__(256) void k_list_best(int64_t n, const int32_t *__restrict__ comp,
                                                    const int32_t *__restrict__ lcnt, const int32_t *__restrict__ lj,
                                                    const float *__restrict__ lv, const float *__restrict__ rn,

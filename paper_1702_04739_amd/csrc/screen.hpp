@@ -25,6 +25,7 @@
 // every column whose O can reach the row's minimum O.
 #pragma once
 
+#include <cfloat>
 #include <vector>
 
 #include "common.hpp"
@@ -182,6 +183,11 @@ __device__ __forceinline__ float pair_bound(const ScreenBound &B, float ri, floa
 // Lower bound of D^2 from Dhat^2 = v and the bound E (both >= 0): the 2^-21
 // slack covers the two roundings of this evaluation.
 __device__ __forceinline__ float lower_of(float v, float E) { return fmaf(-0x1p-21f, v + E, v - E); }
+// The same where v + E overflows too, so that v + E <= (lower + 2 E) (1 + 2^-20)
+// holds as well: the lists of pair-bound data have v's upper bound from that.
+__device__ __forceinline__ float lower_of_large(float v, float E) {
+    return fmaf(-0x1p-21f, fminf(v + E, FLT_MAX), v - E);
+}
 
 // Workgroup-wide initialisation of the per-row state; `row_of(q)` gives the
 // global row of local slot q (or -1).

@@ -715,7 +715,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_screen_pairs(ScreenArgs A, const
                     const float vf = __uint_as_float(v);
                     const float E = pair_bound(A.bound, rr[ib], rj, re_[ib], ej);
                     const uint32_t uU = __float_as_uint(vf + E);
-                    const uint32_t uL = v < INF_BITS ? __float_as_uint(fmaxf(lower_of(vf, E), 0.0f)) : INF_BITS;
+                    const uint32_t uL = v < INF_BITS ? __float_as_uint(fmaxf(lower_of_large(vf, E), 0.0f)) : INF_BITS;
                     mu[ib] = min(mu[ib], uU);
                     ml[ib] = min(ml[ib], uL);
                     cU = min(cU, uU);

@@ -68,3 +68,10 @@ def _half_copies(n, d, spread, seed):
 def test_rows_that_flood_their_list(iso, n, d, spread, precision):
     """More (nearly) equal distances in a tile than a list is offered before it is cut to below its dropped values."""
     _same_tree(iso, _half_copies(n, d, spread, n), None, precision=precision)
+
+
+@pytest.mark.parametrize("n,d,scale", [(8300, 6, 2e18), (9000, 24, 1.6e18), (9000, 24, 1e18)])
+def test_listed_upper_bounds_of_large_distances(iso, n, d, scale):
+    """Squared distances within their error bound of the largest float: a listed pair's upper bound stays one."""
+    X = np.random.default_rng(1000 * n + d).standard_normal((n, d)).astype(np.float32) * np.float32(scale)
+    _same_tree(iso, X, True, precision="bf16", recheck="fp64", pair_bounds=True)
