@@ -124,16 +124,18 @@ typedef struct {
 } iso_mst_info;
 
 /* Device bytes iso_mst needs as workspace for n points in d dimensions (room
- * for the FP32 screen included, which a loose low-precision screen escalates to). */
+ * for the FP32 screen included, which a loose low-precision screen escalates to;
+ * with an FP32 screen up to 4,096 points, room for the distance matrix under
+ * either recheck: 8 n^2 bytes, 134 MB at most). */
 iso_status iso_mst_workspace_size(int64_t n, int64_t d, int32_t precision, size_t *bytes /* host */);
 
 /* Euclidean minimum spanning tree of the complete graph on the n points X
- * (Sec. 2.2 step 2 / Sec. 3.5).  The n x n distance matrix is never stored:
- * distances are formed tile by tile.  Edges are totally ordered by (D^2 under
+ * (Sec. 2.2 step 2 / Sec. 3.5).  In the screened rounds distances are formed
+ * tile by tile and never stored as an n x n matrix.  Edges are totally ordered by (D^2 under
  * `recheck`, smaller end id, larger end id), so the tree is unique.  Rounds
  * screen every inter-component pair, except that a round after the first may
  * be decided by the neighbour lists that the first round's screen (or, for small
- * n, loose bounds or without the bounding-ball test, the second's) builds, and
+ * n, loose bounds, heavy tails or without the bounding-ball test, the second's) builds, and
  * once at most 64 components remain one final round joins them
  * all (both are switched off by ISO_MST_NO_LISTS / ISO_MST_NO_FINAL in
  * `flags`; the tree does not change).  Points are ordered into tiles of nearby
@@ -142,7 +144,9 @@ iso_status iso_mst_workspace_size(int64_t n, int64_t d, int32_t precision, size_
  * bounding-ball test of dual-tree Boruvka; ISO_MST_NO_PRUNE turns it off; the
  * tree does not change).  With an FP32 screen and no flags up to 4,096 points
  * take no screen: the rounds run on the matrix of all exact distances (info:
- * no tile pairs, n (n - 1) / 2 candidates).
+ * no tile pairs, n (n - 1) / 2 candidates), n^2 values of the recheck's
+ * precision in the workspace; a workspace without room for them, and where
+ * the library allocates it a device without, gets the screened rounds.
  *   X       [n*ld] FP32 points (read only).
  *   precision  ISO_PREC_* of the screen;  recheck  ISO_RECHECK_* (edge order);
  *   flags   OR of ISO_MST_NO_* bits, or 0.
@@ -269,8 +273,8 @@ iso_status iso_subpartition_all_k(const int32_t *parent, const double *length, i
  *   omega0[v] = sum over j != v, ascending j, of phi(D(v, j))   (phi_kind ISO_PHI_*),
  *   p0[v]     = alpha * sum over j != v, ascending j, of D(v, j) (exactly 0 when alpha == 0).
  * O(n^2 d) FP64 work.  Either output may be NULL.  X [n*ld] FP32; sigma > 0.
- * Scratch of 8 W^2 bytes (W <= min(n + 63, 4096), 134 MB at most) is allocated with hipMallocAsync on
- * `stream` and released with hipFreeAsync in stream order (no synchronisation).
+ * Scratch of 8 W^2 bytes (W <= min(n + 63, 4096), 134 MB at most; less where that does not fit) is allocated
+ * with hipMallocAsync on `stream` and released with hipFreeAsync in stream order (no synchronisation).
  * Errors: null X, n < 2, d < 1, ld < d, sigma <= 0 or not finite, alpha < 0 or
  * not finite, unknown phi_kind (INVALID_ARG). */
 iso_status iso_graph_weights(const float *X, int64_t n, int64_t d, int64_t ld, double sigma, int32_t phi_kind,

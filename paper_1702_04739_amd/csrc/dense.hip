@@ -3,14 +3,14 @@
 //
 // A call with a few hundred or thousand points is launches, copies and host
 // waits: the tile-pair screen's rounds take some 130 launches and a dozen waits
-// (n = 150, d = 5: 0.75 ms; n = 2048, d = 16: 1.13 ms), while all n^2 / 2 exact
+// (n = 150, d = 5: 0.75 ms; n = 2048, d = 16: 1.08 ms), while all n^2 / 2 exact
 // distances are a few million operations.  So up to DENSE_MAX_N points every
 // pair's D^2 is formed once, in the recheck's own arithmetic, into an n x n
 // matrix that stays in the last-level cache; each Boruvka round is one launch
 // over its rows, whose last workgroup joins the components, and one workgroup
 // roots the tree.  The edge order is that of the rechecked screen, (D^2, smaller
 // id, larger id), and so is the tree.  No host wait before the end.  0.12 and
-// 0.15 ms on those two, half of it the launches.
+// 0.16 ms on those two, half of it the launches.
 #include <cmath>
 
 #include "common.hpp"

@@ -30,10 +30,15 @@ constexpr int GW_K = 16;           // coordinates per LDS stage
 constexpr int GW_R = 4;            // elements per thread and direction of a distance tile
 constexpr int GW_T = 16 * GW_R;    // rows and columns of a distance tile; W is a multiple of it
 // W is at most 4096 points: the buffer (W^2 doubles, 134 MB) then stays in the
-// 256 MB last-level cache between the two kernels.  W is at most 2048 or W^2 at
-// most n * GW_BUF doubles.  At n = 50,000, d = 64 the sums take 6.1 ms with it,
-// against 10.7 ms with W = 6272 (315 MB); with W = 2048 the 256 workgroups of
-// a pair's sums leave the CUs waiting on the exponentials' latency (10.6 ms).
+// 256 MB last-level cache between the two kernels.  At n = 50,000, d = 64 the
+// sums take 6.1 ms with it, against 10.7 ms with W = 6272 (315 MB); with W = 2048
+// the 256 workgroups of a pair's sums leave the CUs waiting on the exponentials'
+// latency (10.6 ms).  And W is at most 2048 or W^2 at most n * GW_BUF: fewer, larger
+// blocks win up to 2048 points (fewer launches) and lose above, where the sums read
+// a buffer several times the L2s' 32 MB (d = 64, ms: n = 2,048 one block 0.14, two
+// 0.17; n = 3,000 two of 1,536 0.21, one 0.42; n = 6,500 three of 2,176 0.54, two of
+// 3,264 0.66; n = 8,000 three of 2,688 0.64, two of 4,032 0.79; but n = 5,000 0.38
+// and 0.34, and at d = 784 1.75 and 1.52; no difference from n = 12,000 on).
 constexpr int64_t GW_BUF = 1024, GW_WMAX = 4096;
 
 // Dt[jj * W + ii] = D(a0 + ii, b0 + jj) for ii < wa, jj < wb: the square root of

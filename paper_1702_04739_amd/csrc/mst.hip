@@ -1,6 +1,7 @@
 // mst.hip -- Euclidean minimum spanning tree on gfx950 by Boruvka rounds over
 // on-the-fly distance tiles (the paper builds the MST with Prim over a stored
-// n x n affinity matrix, Secs. 3.4-3.5; here the matrix is never stored).
+// n x n affinity matrix, Secs. 3.4-3.5; here the matrix is never stored, except
+// for few points, dense.hip).
 //
 // One Boruvka round:
 //   screen    : every unordered pair of points is formed once, tile pair by
@@ -849,8 +850,8 @@ __global__ void k_sample_labels(int64_t npos, int32_t *__restrict__ out) {
 // of a real pair.  Two rows with the same least minimum are each other's nearest
 // (a pair's value is formed once and merged into both): counted in
 // counters[C_MUTUAL].  One workgroup per tile.  (Minima over the tiles 1 .. 5
-// away instead of halves of the own one, third smallest of six: where near tiles hold small clusters, tau
-// reached other clusters and lists overflowed; n = 50,000, d = 16 in clusters
+// away instead of halves of the own one, third smallest of six: where near tiles
+// hold small clusters, tau reached other clusters and lists overflowed; n = 50,000, d = 16 in clusters
 // of 300: 11.4 ms, 5.9 so, 7.1 with the second round's lists.)
 __global__ __launch_bounds__(GT) void k_list_tau(const int32_t *__restrict__ order, int64_t npos, int64_t n,
                            const float *__restrict__ smp,
@@ -1727,11 +1728,11 @@ __global__ void k_pair_scatter(const int2 *__restrict__ pairs, int64_t npairs, c
 //   bound of its lightest outgoing edge (recheck scale): the round needs only
 //   that edge of every component (the pair, within its own row's reach, keeps
 //   the row's capture);
-//   in the round that builds neighbour lists R_i >= tau_i + Emax_i as well
-//   (a list takes the partners with Dhat^2 <= tau_i, and Dhat^2 >= D^2 - Emax_i).
+//   in the round that builds neighbour lists R_i >= tau_i as well (a partner that
+//   the lists miss then has D^2 > tau_i, which is what tau_i says of it).
 // A tile pair with LB^2 > max R over both tiles then holds no edge the round
-// selects and no list entry, so every component's lightest edge, the lists
-// and the tree are those of the full screen (a row whose own lightest edge
+// selects, so every component's lightest edge and the tree are those of the
+// full screen, and the lists bound what they miss (a row whose own lightest edge
 // lies beyond its component's U may keep a larger running minimum, which only
 // bounds its own candidates).
 // Each round screens first the tile pairs whose balls meet (LB = 0), then,
@@ -3710,10 +3711,10 @@ void run_mst(MstPlan &P, Arena &arena, const float *X, int32_t recheck, int32_t 
 // points (16-bit ids, the join's and the rooting's tables in LDS) and
 // DENSE_MAX_WORK coordinate differences, and only where the call leaves
 // everything to the library: a screen precision other than FP32 and any flag
-// ask for the screened rounds.  Both sides, FP32 recheck, us: n = 150, d = 5: 111
-// and 644; n = 2000, d = 16: 159 and 997; n = 4096, d = 16 / 784 / 4096: 238 and
-// 1254 / 996 and 2106 / 4287 and 6641 (FP64 recheck 7511 and 8435: there the work
-// limit lies).
+// ask for the screened rounds.  Both sides (the screened one without lists), normal
+// points, FP32 recheck, us: n = 150, d = 5: 120 and 746; n = 2000, d = 16: 171 and
+// 1071; n = 4096, d = 16 / 784 / 4096: 246 and 1193 / 768 and 1770 / 3103 and 5710
+// (FP64 recheck 6300 and 6628: there the work limit lies).
 constexpr double DENSE_MAX_WORK = 0x1p36;
 
 struct DensePlan {

@@ -3,9 +3,9 @@ wrong, against the FP64 oracle on the same tree: trees at the edges of the
 tiers (32, 1,024 and 16,384 vertices), a caterpillar whose open vertices exceed
 the walking wave's stack (every level keeps one open), paths, hubs with more
 children than a chunk of feeds, and a star with more cut vertices than the
-recorded list holds (the sorting path).  Labels, iterations, bracket and cluster
-sizes are identical, i_k within 1e-12 (the device's and the host's exp differ
-by an ulp); the all-k sweep equals the single-k calls."""
+recorded list holds (the sorting path).  Labels and cluster sizes are identical,
+i_k within 1e-12, iterations within 2 and the bracket within 4 ulp (the device's
+and the host's exp differ by an ulp); the all-k sweep equals the single-k calls."""
 import numpy as np
 import pytest
 
